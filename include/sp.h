@@ -24,6 +24,9 @@
  *   needs more allocates a larger block once and keeps the old one until sp_destroy, so a captured graph
  *   never names freed memory), so they may be captured into a HIP graph on the context's stream.
  *   A plan keeps its context alive: sp_destroy may be called before sp_plan_destroy.
+ *   Decode launches that cut their key lists into pieces use scratch memory that sp_create allocates: 16 regions,
+ *   one per stream (and per stream of a captured graph) the context has launched such a decode on; a launch that
+ *   finds all of them taken runs without and gives the same bits, slower.
  */
 #ifndef SP_H_
 #define SP_H_

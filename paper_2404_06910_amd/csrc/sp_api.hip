@@ -120,9 +120,8 @@ extern "C" const char *sp_version(void) { return "sp-forkjoin 0.1 (gfx950)"; }
 
 extern "C" const char *sp_last_error(const sp_ctx *ctx) { return ctx ? ctx->err.c_str() : g_err.c_str(); }
 
-static void *alloc_sal(int32_t slots, int64_t rows) {
+static void *alloc_zeroed(size_t bytes) {
   void *p = nullptr;
-  const size_t bytes = sp::saliency_scratch_bytes(rows, slots);
   if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
   // zero before any stream may use it: the memset runs on the null stream, the kernels on the caller's
   if (hipMemset(p, 0, bytes) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) {
@@ -131,6 +130,8 @@ static void *alloc_sal(int32_t slots, int64_t rows) {
   }
   return p;
 }
+
+static void *alloc_sal(int32_t slots, int64_t rows) { return alloc_zeroed(sp::saliency_scratch_bytes(rows, slots)); }
 
 extern "C" sp_status sp_create(sp_ctx **out, int device, void *hip_stream) {
   if (!out) return fail(nullptr, SP_ERR_INVALID_ARG, "out is NULL");
@@ -152,8 +153,10 @@ extern "C" sp_status sp_create(sp_ctx **out, int device, void *hip_stream) {
   c->sal_slots = sp::kSalDefaultSlots;
   c->sal_rows = sp::kSalDefaultRows;
   c->sal = alloc_sal(c->sal_slots, c->sal_rows);
-  if (!c->sal || hipEventCreateWithFlags(&c->stage_ev, hipEventDisableTiming) != hipSuccess) {
+  c->dec = alloc_zeroed(sp::kDecRegionBytes * sp::kDecRegions);
+  if (!c->sal || !c->dec || hipEventCreateWithFlags(&c->stage_ev, hipEventDisableTiming) != hipSuccess) {
     if (c->sal) (void)hipFree(c->sal);
+    if (c->dec) (void)hipFree(c->dec);
     delete c;
     return fail(nullptr, SP_ERR_WORKSPACE, "could not allocate the context's workspace");
   }
@@ -162,7 +165,9 @@ extern "C" sp_status sp_create(sp_ctx **out, int device, void *hip_stream) {
 }
 
 static void ctx_unref(sp_ctx *ctx) {
-  if (--ctx->refs == 0) delete ctx;
+  if (--ctx->refs) return;
+  if (ctx->dec) (void)hipFree(ctx->dec);
+  delete ctx;
 }
 
 extern "C" void sp_destroy(sp_ctx *ctx) {
@@ -209,6 +214,27 @@ static sp_status ensure_sal(sp_ctx *ctx, int64_t n_rows, int32_t n_slots) {
   ctx->sal_slots = slots;
   ctx->sal_rows = rows;
   return SP_OK;
+}
+
+// The region of the order of execution that a launch on `s` joins.  hipStreamPerThread names another stream in every
+// thread and gets none; neither does a launch for which all regions are taken.
+void *sp::decode_region(sp_ctx *ctx, hipStream_t s) {
+  if (s == hipStreamPerThread) return nullptr;
+  unsigned long long capture = 0;
+  if (s) {                                              // the null stream cannot be captured
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    if (hipStreamGetCaptureInfo(s, &st, &id) != hipSuccess) return nullptr;
+    if (st != hipStreamCaptureStatusNone) capture = id + 1;
+  }
+  size_t i = 0;
+  for (; i < ctx->dec_owner.size(); ++i)
+    if (ctx->dec_owner[i].stream == s && ctx->dec_owner[i].capture == capture) break;
+  if (i == ctx->dec_owner.size()) {
+    if (i == size_t(sp::kDecRegions)) return nullptr;
+    ctx->dec_owner.push_back({s, capture});
+  }
+  return static_cast<char *>(ctx->dec) + i * sp::kDecRegionBytes;
 }
 
 namespace {
@@ -500,6 +526,9 @@ sp_status build_plan(sp_ctx *ctx, const sp_segtable *t, int32_t n_q_heads, int32
       if (t->seg_path[s] < 0) push_range(p->dec_ranges, first, t->seg_tok_start[s], t->seg_tok_len[s]);
       else segs_of_path[t->seg_path[s]].push_back(s);
     }
+    int64_t shared_keys = 0;
+    for (size_t r = first; r < p->dec_ranges.size(); ++r) shared_keys += p->dec_ranges[r].len;
+    p->max_shared_keys = std::max(p->max_shared_keys, shared_keys);
     p->shared_rng_beg[b] = static_cast<int32_t>(first);
     p->shared_rng_end[b] = static_cast<int32_t>(p->dec_ranges.size());
     for (int32_t q = 0; q < np; ++q) {
@@ -509,6 +538,9 @@ sp_status build_plan(sp_ctx *ctx, const sp_segtable *t, int32_t n_q_heads, int32
       p->path_rng_beg[slot] = static_cast<int32_t>(pf);
       p->path_rng_end[slot] = static_cast<int32_t>(p->dec_ranges.size());
       p->path_max_ranges[b] = std::max(p->path_max_ranges[b], int32_t(p->dec_ranges.size() - pf));
+      int64_t path_keys = 0;
+      for (size_t r = pf; r < p->dec_ranges.size(); ++r) path_keys += p->dec_ranges[r].len;
+      p->max_path_keys = std::max(p->max_path_keys, path_keys);
     }
   }
   return SP_OK;

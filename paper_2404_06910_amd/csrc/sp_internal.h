@@ -36,6 +36,14 @@ inline size_t saliency_scratch_bytes(int64_t rows, int32_t slots) {
 }
 constexpr size_t kSalStaticBytes = 256 + size_t(kSalStaticRows) * sizeof(RowLp) + sizeof(SalSlot) * size_t(kSalStaticSlots);
 
+// Scratch of a decode launch whose key lists are cut into pieces: partial sums of at most kDecPartRows (query row,
+// piece) pairs of up to 128 dims plus {max, sum} each, then the arrival counters (zero between launches).
+constexpr int64_t kDecPartRows = 4096;
+constexpr int kDecPartCounters = 1024;
+constexpr size_t kDecPartBytes = size_t(kDecPartRows) * (128 + 2) * 4;
+constexpr size_t kDecRegionBytes = kDecPartBytes + size_t(kDecPartCounters) * 4;
+constexpr int kDecRegions = 16;
+
 // A run of segments fused on the query side: child segments that are packed directly behind
 // their parent continue the parent's causal sequence (Sec. 3.2: a chain is a classical prompt).
 // Rows [tok_start, tok_start+len) see: the ancestor ranges (all keys), then own rows causally.
@@ -115,6 +123,12 @@ struct sp_ctx {
   hipEvent_t stage_ev = nullptr;
   bool stage_busy = false;
   std::vector<std::pair<void *, size_t>> blob_pool;
+  // Decode scratch: kDecRegions regions of one block, made in sp_create.  A region belongs to one order of execution --
+  // a stream, or a stream within one capture -- for as long as the context lives, so that launches that may overlap
+  // never share one.  The block is freed with the last plan (a captured decode may be replayed until then).
+  struct DecodeOwner { hipStream_t stream; unsigned long long capture; };
+  void *dec = nullptr;
+  std::vector<DecodeOwner> dec_owner;
   int refs = 1;               // the context itself + every live plan made on it
   bool closed = false;        // sp_destroy was called; the struct lives on until the last plan is gone
 };
@@ -132,6 +146,7 @@ struct sp_plan {
   int32_t max_ranges = 0;
   int32_t max_dec_ranges = 0; // largest joined-cache range count bound per prompt (shared + per-path max)
   int64_t visible_pairs = 0;
+  int64_t max_shared_keys = 0, max_path_keys = 0;   // most tokens of a prompt's shared part / of any path
   bool has_pos = false, has_slopes = false;
   // host copies
   std::vector<int32_t> prompt_seg_off, seg_tok_start, seg_tok_len, seg_parent, seg_path;
@@ -186,6 +201,8 @@ struct DecodeArgs {
   void *o_out;
   float scale;
 };
+// Scratch region for a decode launch on stream s, or nullptr when all are taken (the launch then does without).
+void *decode_region(sp_ctx *ctx, hipStream_t s);
 hipError_t launch_decode(const sp_plan *plan, const DecodeArgs &a, hipStream_t s);
 
 }  // namespace sp
