@@ -387,14 +387,6 @@ sp_status build_plan(sp_ctx *ctx, const sp_segtable *t, int32_t n_q_heads, int32
       p->visible_pairs += n * rg.anc_keys + (int64_t(iv.second) * (iv.second + 1) - int64_t(iv.first) * (iv.first + 1)) / 2;
     }
   }
-  // device copy of the token -> group map: tokens of cached segments produce no rows (fp32 kernel only)
-  if (dtype == SP_F32) {
-    p->tok_group_dev = p->tok_group;
-    for (int32_t s = 0; s < S; ++s)
-      if (is_cached(s))
-        std::fill(p->tok_group_dev.begin() + t->seg_tok_start[s],
-                  p->tok_group_dev.begin() + t->seg_tok_start[s] + t->seg_tok_len[s], -1);
-  }
 
   const int32_t G = n_q_heads / n_kv_heads;
   const int n_cu = ctx ? ctx->n_cu : 256;
@@ -496,6 +488,8 @@ sp_status build_plan(sp_ctx *ctx, const sp_segtable *t, int32_t n_q_heads, int32
     const int32_t rounds = 8 / p->waves_per_wg;
     static const int32_t four[4] = {1000, 1085, 1085, 1125}, two[2] = {1000, 1150}, one[1] = {1000};
     hand_out(cost, p->n_wg, rounds == 4 ? four : rounds == 2 ? two : one, rounds, owner, p->wg_begin);
+    p->max_slice = 0;
+    for (int32_t i = 0; i < p->n_wg; ++i) p->max_slice = std::max(p->max_slice, p->wg_begin[i + 1] - p->wg_begin[i]);
     p->items.resize(n_items);
     std::vector<int32_t> at(p->wg_begin.begin(), p->wg_begin.end() - 1);
     size_t i = 0;
@@ -569,11 +563,9 @@ sp_status upload_plan(sp_ctx *ctx, sp_plan *p, void *reuse_blob, size_t reuse_by
     off += bytes + 16;
     return pieces.back().at;
   };
-  const size_t o_groups = add(p->groups.data(), p->groups.size() * sizeof(sp::RowGroup)),
-               o_ranges = add(p->ranges.data(), p->ranges.size() * sizeof(sp::KeyRange)),
+  const size_t o_ranges = add(p->ranges.data(), p->ranges.size() * sizeof(sp::KeyRange)),
                o_items = add(p->items.data(), p->items.size() * sizeof(sp::WorkItem)),
                o_wgb = add(p->wg_begin.data(), p->wg_begin.size() * 4),
-               o_tokg = add(p->tok_group_dev.data(), p->tok_group_dev.size() * 4),
                o_pos = add(p->pos.data(), p->pos.size() * 4), o_slopes = add(p->slopes.data(), p->slopes.size() * 4),
                o_poff = add(p->path_off.data(), p->path_off.size() * 4),
                o_sd = add(shared_desc.data(), shared_desc.size() * sizeof(sp::RangeDesc)),
@@ -631,11 +623,9 @@ sp_status upload_plan(sp_ctx *ctx, sp_plan *p, void *reuse_blob, size_t reuse_by
   char *base = static_cast<char *>(blob);
   sp::PlanDev &d = p->dev;
   d = sp::PlanDev{};
-  d.groups = reinterpret_cast<const sp::RowGroup *>(base + o_groups);
   d.ranges = reinterpret_cast<const sp::KeyRange *>(base + o_ranges);
   d.items = reinterpret_cast<const sp::WorkItem *>(base + o_items);
   d.wg_begin = reinterpret_cast<const int32_t *>(base + o_wgb);
-  d.tok_group = reinterpret_cast<const int32_t *>(base + o_tokg);
   d.tok_pos = p->pos.empty() ? nullptr : reinterpret_cast<const float *>(base + o_pos);
   d.slopes = p->slopes.empty() ? nullptr : reinterpret_cast<const float *>(base + o_slopes);
   d.path_off = reinterpret_cast<const int32_t *>(base + o_poff);

@@ -82,11 +82,9 @@ struct WorkItem {
 
 // Device-side view of a plan (plain pointers, passed by value to kernels).
 struct PlanDev {
-  const RowGroup *groups;
   const KeyRange *ranges;
   const WorkItem *items;
   const int32_t *wg_begin;       // [n_wg + 1] slice of the (permuted) work list per workgroup slot
-  const int32_t *tok_group;      // [n_tokens] row group of each token, -1 = uncovered
   const float *tok_pos;          // [n_tokens] or nullptr
   const float *slopes;           // [n_q_heads] or nullptr
   // decode tables
@@ -142,7 +140,8 @@ struct sp_plan {
   int32_t waves_per_wg = 4;   // waves (32-row blocks) per prefill workgroup
   int32_t tile_rows = 0;      // token rows per prefill tile
   int32_t n_tiles = 0;
-  int32_t n_wg = 0;           // persistent prefill workgroups (a multiple of 8)
+  int32_t n_wg = 0;           // slots of the prefill work list (a multiple of 8): persistent workgroups, or items of a round
+  int32_t max_slice = 0;      // most work items of any slot
   int32_t max_ranges = 0;
   int32_t max_dec_ranges = 0; // largest joined-cache range count bound per prompt (shared + per-path max)
   int64_t visible_pairs = 0;
@@ -155,7 +154,6 @@ struct sp_plan {
   std::vector<sp::WorkItem> items;
   std::vector<int32_t> wg_begin;
   std::vector<int32_t> tok_group;      // token -> row group (host inspection)
-  std::vector<int32_t> tok_group_dev;  // the same with tokens of cached segments set to -1
   std::vector<int32_t> path_off, shared_rng_beg, shared_rng_end, path_rng_beg, path_rng_end;
   std::vector<sp::KeyRange> dec_ranges;
   std::vector<int32_t> path_max_ranges;  // per prompt: max ranges of any single path

@@ -1,103 +1,297 @@
-// a1 (fp32 storage): ForkJoin prefill attention over the prompt DAG (Sec. 3.2, 3.2.1; App. B.3)
-// in plain fp32 vector arithmetic.  This is the precision path (tolerance 1e-4); the bf16 path
-// uses the matrix cores.  One wave handles one (token, query head) row: the lanes split the head
-// dimension, the row's visible keys (ancestor ranges root-to-leaf, then its own run causally)
-// are visited in order with an online softmax, four keys per step.
+// a1 (fp32 storage): ForkJoin prefill attention over the prompt DAG (Sec. 3.2, 3.2.1; App. B.3), the precision path
+// (tolerance 1e-4), on the fp32 matrix instruction: inputs, products, sums and probabilities stay in 32 bits.
+//
+// A work item of the plan is up to 32*NW/HPW consecutive rows of one row group for HPW query heads that share a KV head.
+// It is done by 2*NW one-wave workgroups; a wave owns 16 of its rows of one head and walks the rows' keys (ancestor ranges
+// root to leaf, then the own run up to its last row) 16 at a time.  Per step, with v_mfma_f32_16x16x4_f32:
+//   S^T[key, row] = K[key, :] . Q[row, :]        A = K, B = Q (registers for the whole item)
+//   O^T[d, row]  += V^T[d, key] . P^T[key, row]  A = V, B = P as the first product leaves it
+// Lane L holds row L % 16 throughout: accumulator register r of a 16x16 tile is its row 4 * (L / 16) + r, which is also
+// the k-slot that lane feeds in the second product when slot L / 16 of step r is bound to key 4 * (L / 16) + r.  So the
+// probabilities never move.  The k-slots of the first product and the rows of O^T are bound so that every lane reads and
+// writes 16-byte vectors: dims 16i + 4 * (L / 16) + e of K and Q, dims 64h + 4 * (L % 16) + e of V.
+//
+// What bounds it: the matrix pipe (a loop of these products alone sustains 120 TFLOP/s on this part).  K and V fragments
+// are loaded straight from memory into registers, V under the first product, the next K under the second, and no wave
+// waits for another.  16 rows per wave and not 32: a masked half of a diagonal tile and an unfilled last tile cost half as
+// much, and the waves are short enough for the last of them to end together.  Sums are kept in short chains that are then
+// added up: one chain of D products (and one of all keys for O) has twice the error of the vector kernel that was here
+// before, the short ones have 0.80 to 0.99 of its error against 64 bits.
+// Measured, one prompt of 20 documents of 64-220 tokens, 32 heads of 128 dims (9.9 GFLOP): 712 us with one wave per row in
+// vector arithmetic, 161 us now (in a profiled run 176; there 194 us with the waves of an item in one workgroup (it keeps its place until its longest
+// wave ends, and 209 us with K and V staged through LDS for the four waves of an item).
 #include "sp_device.h"
 #include "sp_internal.h"
 
 namespace sp {
 
-template <int D>
-__global__ __launch_bounds__(256) void prefill_f32_kernel(PlanDev pd, const float *__restrict__ Q,
-                                                          const float *__restrict__ K,
-                                                          const float *__restrict__ V, float *__restrict__ O,
-                                                          int64_t q_ts, int64_t q_hs, int64_t kv_ts, int64_t kv_hs,
-                                                          float scale) {
-  // 16 lanes cover one key row with 16-byte loads (D = 64: 4 floats per lane; D = 128: 2 loads)
-  constexpr int EPL = D / 16;            // elements per lane
-  const int Hq = pd.n_q_heads, G = Hq / pd.n_kv_heads;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t row_id = (int64_t)blockIdx.x * 4 + wave;
-  if (row_id >= (int64_t)pd.n_tokens * Hq) return;
-  const int tok = int(row_id / Hq), h = int(row_id % Hq), g = h / G;
-  const int grp = pd.tok_group[tok];
-  if (grp < 0) return;
-  const RowGroup rg = pd.groups[grp];
-  const int n_vis = rg.anc_keys + (tok - rg.tok_start) + 1;
-  const int quad = lane >> 4, sub = lane & 15;       // 4 keys in flight per wave
-  const bool bias = pd.slopes != nullptr;
-  const float slope2 = bias ? pd.slopes[h] * kLog2e : 0.f;
-  const float pos_q = bias ? pd.tok_pos[tok] : 0.f;
+namespace {
 
-  float qf[EPL];
-  {
-    const float *qp = Q + (int64_t)tok * q_ts + (int64_t)h * q_hs + sub * EPL;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) qf[e] = qp[e] * (scale * kLog2e);
-  }
-  float m = kNegBig, l = 0.f, acc[EPL];
-#pragma unroll
-  for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
+// value of a row's four lanes (L, L ^ 16, L ^ 32, L ^ 48) combined
+__device__ __forceinline__ float quad_max(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float quad_sum(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
 
-  for (int vk0 = 0; vk0 < n_vis; vk0 += 4) {
-    const int vk = vk0 + quad;
-    const bool ok = vk < n_vis;
-    // virtual key index -> packed token: walk the ancestor ranges, else own run
-    int ktok = rg.tok_start + (vk - rg.anc_keys);
-    if (!ok) ktok = tok;
-    else if (vk < rg.anc_keys) {
-      int rem = vk;
-      for (int r = 0; r < rg.n_ranges; ++r) {
-        const KeyRange kr = pd.ranges[rg.range_off + r];
-        if (rem < kr.len) { ktok = kr.tok_start + rem; break; }
-        rem -= kr.len;
+}  // namespace
+
+template <int D, int HPW, int NW, bool BIAS>
+__global__ __launch_bounds__(64, 2) void prefill_f32_kernel(PlanDev pd, const float *__restrict__ Q,
+                                                                  const float *__restrict__ K,
+                                                                  const float *__restrict__ V, float *__restrict__ O,
+                                                                  int64_t q_ts, int64_t q_hs, int64_t kv_ts,
+                                                                  int64_t kv_hs, float scale) {
+  constexpr int NI = D / 16;             // 16-byte vectors of a K or Q row per lane; 16-wide blocks of O^T
+  constexpr int NH = D / 64;
+  // A block is one wave.  Blocks are dealt round-robin over the 8 XCDs and started in order: the 2 * NW waves of an item
+  // follow each other on one XCD, and an XCD works on a window of consecutive items of its own range of the list (slot
+  // x * (n_wg / 8) + i holds the items of XCD x that are i-th in its order, then the (i + n_wg / 8)-th, and so on).
+  const int xcd = blockIdx.x % 8, nth = blockIdx.x / 8, wave = nth % (2 * NW), per_xcd = pd.n_wg / 8;
+  const int slot = xcd * per_xcd + (nth / (2 * NW)) % per_xcd;
+  const int item = pd.wg_begin[slot] + nth / (2 * NW * per_xcd);
+  if (item >= pd.wg_begin[slot + 1]) return;
+  const WorkItem w = pd.items[item];
+
+  const int lane = threadIdx.x;
+  const int l16 = lane & 15, quad = lane >> 4;
+  const int head = (w.head0 & 0xffff) + wave % HPW;
+  const int r0 = 16 * (wave / HPW);                          // first tile row of this wave
+  if (r0 >= w.n_rows) return;
+  const int rows = min(16, w.n_rows - r0);
+  const int row = r0 + min(l16, rows - 1);                   // lanes past the tile repeat its last row
+  const int row_tok = w.tok_start + w.row0 + row;
+  const int my_limit = w.anc_keys + w.row0 + row;            // last virtual key that this lane's row sees
+  const int first_limit = w.anc_keys + w.row0 + r0, last_limit = first_limit + rows - 1;
+  const float *Kh = K + int64_t(w.head0 >> 16) * kv_hs + 4 * quad;
+  const float *Vg = V + int64_t(w.head0 >> 16) * kv_hs, *Vh = Vg + 4 * l16;
+
+  // The key range that holds virtual key `base`: [base, base + len) are the tokens from tok on.  Range n_ranges is the
+  // own run.  base, len and tok are the same for all lanes.
+  int rng = -1, base = 0, len = 0, tok = 0;
+  auto seek = [&](int vk) {
+    while (vk >= base + len) {
+      base += len;
+      if (++rng < w.n_ranges) {
+        const KeyRange kr = pd.ranges[w.range_off + rng];
+        tok = kr.tok_start;
+        len = kr.len;
+      } else {
+        tok = w.tok_start;
+        len = 0x7fffffff - base;
       }
     }
-    const float *kp = K + (int64_t)ktok * kv_ts + (int64_t)g * kv_hs + sub * EPL;
-    const float *vp = V + (int64_t)ktok * kv_ts + (int64_t)g * kv_hs + sub * EPL;
-    float d = 0.f, vf[EPL];
+  };
+  // token of virtual key vk >= base; keys behind the last visible one (masked) repeat that one
+  auto token_of = [&](int vk) -> int {
+    int r = rng, b = base, n = len, t = tok;
+    vk = min(vk, last_limit);
+    while (vk >= b + n) {
+      b += n;
+      if (++r < w.n_ranges) {
+        const KeyRange kr = pd.ranges[w.range_off + r];
+        t = kr.tok_start;
+        n = kr.len;
+      } else {
+        t = w.tok_start;
+        n = 0x7fffffff - b;
+      }
+    }
+    return t + (vk - b);
+  };
+
+  float q[4 * NI];
+  {
+    const float *qp = Q + int64_t(row_tok) * q_ts + int64_t(head) * q_hs + 4 * quad;
+    const float scale2 = scale * kLog2e;
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) { d = fmaf(qf[e], kp[e], d); vf[e] = vp[e]; }
+    for (int i = 0; i < NI; ++i) {
+      const f32x4 v = *reinterpret_cast<const f32x4 *>(qp + 16 * i);
 #pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) d += __shfl_xor(d, off);
-    float t = -INFINITY;
-    if (ok) t = bias ? d - slope2 * (pos_q - pd.tok_pos[ktok]) : d;
-    // maximum over the 4 keys of this step (lanes 16 and 32 apart)
-    float mx = fmaxf(t, __shfl_xor(t, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-    const float m_new = fmaxf(m, mx);
-    const float alpha = fast_exp2(m - m_new);
-    const float p = fast_exp2(t - m_new);
-    m = m_new;
-    l = l * alpha + p;                 // per-quad partial sums, combined at the end
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] = fmaf(p, vf[e], acc[e] * alpha);
+      for (int e = 0; e < 4; ++e) q[4 * i + e] = v[e] * scale2;
+    }
   }
-  // combine the four quads (all share the same running maximum m)
-  l += __shfl_xor(l, 16); l += __shfl_xor(l, 32);
+  const float slope2 = BIAS ? pd.slopes[head] * kLog2e : 0.f;
+  const float pos_q = BIAS ? pd.tok_pos[row_tok] : 0.f;
+
+  f32x4 o[NI];                       // o[4h + c][r]: dim 64h + 16 quad + 4r + c of this lane's row
 #pragma unroll
-  for (int e = 0; e < EPL; ++e) { acc[e] += __shfl_xor(acc[e], 16); acc[e] += __shfl_xor(acc[e], 32); }
-  if (quad == 0) {
-    float *op = O + (int64_t)tok * q_ts + (int64_t)h * q_hs + sub * EPL;
-    const float inv = 1.f / l;
+  for (int c = 0; c < NI; ++c)
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) op[e] = acc[e] * inv;
+    for (int r = 0; r < 4; ++r) o[c][r] = 0.f;
+  float m = kNegBig, l = 0.f;
+  f32x4 kf[NI], vf[NI][4];           // vf[h][r]: dims 64h + 4 l16 + (0..3) of key 4 quad + r
+  int vtok[4];                       // tokens of keys 4 quad + r of the step whose K is in kf
+
+  auto load_k = [&](int vk0) {
+    seek(vk0);
+    int ktok;
+    if (vk0 + 15 < base + len && vk0 + 15 <= last_limit) {   // 16 consecutive tokens
+      const int t0 = tok + (vk0 - base);
+      ktok = t0 + l16;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) vtok[r] = t0 + 4 * quad + r;
+    } else {
+      ktok = token_of(vk0 + l16);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) vtok[r] = __shfl(ktok, 4 * quad + r);
+    }
+    const float *kp = Kh + int64_t(ktok) * kv_ts;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) kf[i] = *reinterpret_cast<const f32x4 *>(kp + 16 * i);
+  };
+
+  load_k(0);
+  for (int vk0 = 0; vk0 <= last_limit; vk0 += 16) {
+    float kpos[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float *vp = Vh + int64_t(vtok[r]) * kv_ts;
+#pragma unroll
+      for (int h = 0; h < NH; ++h) vf[h][r] = *reinterpret_cast<const f32x4 *>(vp + 64 * h);
+      if (BIAS) kpos[r] = pd.tok_pos[vtok[r]];
+    }
+    const int step_tok[4] = {vtok[0], vtok[1], vtok[2], vtok[3]};
+
+    // one short chain of products per 16 dims, added up pairwise: the rounding of a single chain of D products is
+    // several times larger
+    f32x4 s[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+      a = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][0], q[4 * i], a, 0, 0, 0);
+      b = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][1], q[4 * i + 1], b, 0, 0, 0);
+      a = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][2], q[4 * i + 2], a, 0, 0, 0);
+      b = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][3], q[4 * i + 3], b, 0, 0, 0);
+      s[i] = a + b;
+    }
+#pragma unroll
+    for (int n = NI / 2; n >= 1; n /= 2)
+#pragma unroll
+      for (int i = 0; i < n; ++i) s[i] += s[i + n];
+    if (vk0 + 16 <= last_limit) load_k(vk0 + 16);
+
+    const bool diag = vk0 + 15 > first_limit;                // some row sees only part of these keys
+    float t[4], p[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      t[r] = s[0][r];
+      if (BIAS) t[r] -= slope2 * (pos_q - kpos[r]);
+      if (diag && vk0 + 4 * quad + r > my_limit) t[r] = -INFINITY;
+    }
+    const float mx = quad_max(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3])));
+    // the reference maximum may lag by up to 8 (a factor of 256 in p and in both sums): nothing to rescale then
+    if (__any(mx > m + 8.f)) {
+      const float m_new = fmaxf(m, mx), alpha = fast_exp2(m - m_new);
+      m = m_new;
+      l *= alpha;
+#pragma unroll
+      for (int c = 0; c < NI; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[c][r] *= alpha;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) p[r] = fast_exp2(t[r] - m);
+    l += (p[0] + p[1]) + (p[2] + p[3]);
+
+    bool plain = true;
+    if (diag) {
+      // The product below multiplies the V row of a key that a row does not see by zero, which leaves no trace only
+      // while that V row is finite.
+      float z = 0.f;
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) z = fmaf(vf[h][r][c], 0.f, z);
+      plain = !__any(z != 0.f);
+    }
+    if (plain) {
+      // a sum of its own per 16 keys, for the same reason
+#pragma unroll
+      for (int h = 0; h < NH; ++h) {
+        f32x4 a[4], b[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) a[c] = b[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int r = 0; r < 4; r += 2)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            a[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[h][r][c], p[r], a[c], 0, 0, 0);
+            b[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[h][r + 1][c], p[r + 1], b[c], 0, 0, 0);
+          }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) o[4 * h + c] += a[c] + b[c];
+      }
+    } else {
+      for (int kk = 0; kk < 16; ++kk) {
+        const int src = 16 * (kk >> 2);
+        const float p0 = __shfl(p[0], src + l16), p1 = __shfl(p[1], src + l16), p2 = __shfl(p[2], src + l16),
+                    p3 = __shfl(p[3], src + l16);
+        const int t0 = __shfl(step_tok[0], src), t1 = __shfl(step_tok[1], src), t2 = __shfl(step_tok[2], src),
+                  t3 = __shfl(step_tok[3], src);
+        const int e = kk & 3;
+        const float pk = e == 0 ? p0 : e == 1 ? p1 : e == 2 ? p2 : p3;
+        const int tk = e == 0 ? t0 : e == 1 ? t1 : e == 2 ? t2 : t3;
+        if (vk0 + kk > my_limit) continue;
+        const float *vp = Vg + int64_t(tk) * kv_ts + 16 * quad;
+#pragma unroll
+        for (int c = 0; c < NI; ++c)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) o[c][r] = fmaf(pk, vp[64 * (c / 4) + 4 * r + c % 4], o[c][r]);
+      }
+    }
+  }
+
+  const float inv = 1.f / quad_sum(l);
+  if (l16 >= rows) return;
+  float *op = O + int64_t(row_tok) * q_ts + int64_t(head) * q_hs + 16 * quad;
+#pragma unroll
+  for (int h = 0; h < NH; ++h)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      f32x4 v;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) v[c] = o[4 * h + c][r] * inv;
+      *reinterpret_cast<f32x4 *>(op + 64 * h + 4 * r) = v;
+    }
+}
+
+template <int D, int HPW, int NW>
+static hipError_t launch_hpw(const sp_plan *plan, const PrefillArgs &a, hipStream_t s) {
+  const dim3 grid(unsigned(plan->n_wg) * unsigned(plan->max_slice) * 2 * NW);
+  if (grid.x == 0) return hipSuccess;                        // nothing is computed: every segment is cached
+  const float *Q = static_cast<const float *>(a.Q), *K = static_cast<const float *>(a.K),
+              *V = static_cast<const float *>(a.V);
+  float *O = static_cast<float *>(a.O);
+  if (plan->has_slopes)
+    hipLaunchKernelGGL((prefill_f32_kernel<D, HPW, NW, true>), grid, dim3(64), 0, s, plan->dev, Q, K, V, O,
+                       a.q_tok_stride, a.q_head_stride, a.kv_tok_stride, a.kv_head_stride, a.scale);
+  else
+    hipLaunchKernelGGL((prefill_f32_kernel<D, HPW, NW, false>), grid, dim3(64), 0, s, plan->dev, Q, K, V, O,
+                       a.q_tok_stride, a.q_head_stride, a.kv_tok_stride, a.kv_head_stride, a.scale);
+  return hipGetLastError();
+}
+
+template <int D>
+static hipError_t launch_d(const sp_plan *plan, const PrefillArgs &a, hipStream_t s) {
+  switch (plan->heads_per_wg) {
+    case 4: return launch_hpw<D, 4, 4>(plan, a, s);
+    case 2: return launch_hpw<D, 2, 2>(plan, a, s);
+    default: return launch_hpw<D, 1, 2>(plan, a, s);
   }
 }
 
 hipError_t launch_prefill_f32(const sp_plan *plan, const PrefillArgs &a, hipStream_t s) {
-  const int64_t rows = (int64_t)plan->n_tokens * plan->n_q_heads;
-  const dim3 grid(unsigned((rows + 3) / 4));
-  if (plan->head_dim == 128)
-    hipLaunchKernelGGL(prefill_f32_kernel<128>, grid, dim3(256), 0, s, plan->dev, static_cast<const float *>(a.Q),
-                       static_cast<const float *>(a.K), static_cast<const float *>(a.V), static_cast<float *>(a.O),
-                       a.q_tok_stride, a.q_head_stride, a.kv_tok_stride, a.kv_head_stride, a.scale);
-  else
-    hipLaunchKernelGGL(prefill_f32_kernel<64>, grid, dim3(256), 0, s, plan->dev, static_cast<const float *>(a.Q),
-                       static_cast<const float *>(a.K), static_cast<const float *>(a.V), static_cast<float *>(a.O),
-                       a.q_tok_stride, a.q_head_stride, a.kv_tok_stride, a.kv_head_stride, a.scale);
-  return hipGetLastError();
+  return plan->head_dim == 128 ? launch_d<128>(plan, a, s) : launch_d<64>(plan, a, s);
 }
 
 }  // namespace sp
