@@ -20,21 +20,23 @@ struct SalSlot {
   uint32_t count;
   uint32_t flags;           // 1: a row with lp = -inf, 2: +inf, 4: NaN
 };
-// per-row result of the saliency row kernel: the log-likelihood in fixed point, or flag bits when it is
-// not finite; scored = 0 for rows without a target
-struct RowLp {
-  long long q;
-  uint32_t flags;
+// what the saliency row kernel leaves of a piece of a row: maximum, sum of exp(x - maximum), the target's logit (first
+// piece) and whether the row has a target
+struct RowPart {
+  float m, s, x_target;
   uint32_t scored;
 };
+// Rows are cut into pieces only while rows * pieces stays at or below this, which the scratch of any call can hold.
+constexpr int64_t kSalSplitRows = 2048;
 constexpr int64_t kSalDefaultRows = int64_t(1) << 16;               // what a new context's workspace is sized for
 constexpr int kSalDefaultSlots = 16384;
 constexpr int64_t kSalStaticRows = int64_t(1) << 16;                // limits of the no-allocation entry point
 constexpr int kSalStaticSlots = 16384;
 inline size_t saliency_scratch_bytes(int64_t rows, int32_t slots) {
-  return 256 + sizeof(SalSlot) * size_t(slots) + sizeof(RowLp) * size_t(rows);
+  return 256 + sizeof(SalSlot) * size_t(slots) + sizeof(RowPart) * size_t(rows);
 }
-constexpr size_t kSalStaticBytes = 256 + size_t(kSalStaticRows) * sizeof(RowLp) + sizeof(SalSlot) * size_t(kSalStaticSlots);
+static_assert(kSalSplitRows <= kSalDefaultRows && kSalSplitRows <= kSalStaticRows, "pieces of a call fit its scratch");
+constexpr size_t kSalStaticBytes = 256 + size_t(kSalStaticRows) * sizeof(RowPart) + sizeof(SalSlot) * size_t(kSalStaticSlots);
 
 // Scratch of a decode launch whose key lists are cut into pieces: partial sums of at most kDecPartRows (query row,
 // piece) pairs of up to 128 dims plus {max, sum} each, then the arrival counters (zero between launches).

@@ -1,16 +1,17 @@
 // a2: Bayesian path saliency (Sec. 3.2.3; App. B.1 Eq. 2).
 //
-// Kernel 1 (HBM-bound, one workgroup per scored logit row) streams the row once and stores the
-// log-likelihood of its target token, lp = x[target] - logsumexp(x), as 64-bit fixed point (2^-36 units),
-// with one plain store.  It touches no atomic: a workgroup is not retired before its memory operations are
-// acknowledged, and a device-scope atomic takes microseconds to come back while HBM is saturated (measured:
-// 16 to 42 us per launch, whether the kernel waits for its atomics or not).
-// Kernel 2 (one thread per row, a few dozen workgroups) reduces per path slot without floating-point
-// atomics and without rescanning the rows per slot: every row adds its value to its slot with an INTEGER
-// atomic -- integer addition is associative, so the sum does not depend on the order of arrival and equal
-// inputs give bit-identical scores; rows whose lp is not finite set a flag bit instead.  A counter finds
-// the workgroup that finishes last; it turns the sums into scores (SUM or MEAN, plus the prior) and puts
-// every accumulator back to zero, the state the next launch expects.
+// Kernel 1 (HBM-bound, one workgroup per scored logit row, or per piece of one) streams the row once and stores the
+// maximum m and the sum of exp(x - m) with one plain store.  It touches no atomic: a workgroup is not retired before its
+// memory operations are acknowledged, and a device-scope atomic takes microseconds to come back while HBM is saturated
+// (measured: 16 to 42 us per launch, whether the kernel waits for its atomics or not).
+// Kernel 2 merges a row's pieces in order, lp = x[target] - logsumexp(x) as 64-bit fixed point (2^-36 units), and adds up
+// the rows of each path.  Integer addition is associative, so the sum does not depend on an order and equal inputs give
+// bit-identical scores; a row whose lp is not finite becomes a flag bit instead.
+//   scan: one workgroup per path slot reads the path of every row and sums the rows that are its own;
+//   atomic, where slots times rows would be too much to read: one thread per row, integer atomics per slot, and a counter
+//   that finds the workgroup that finishes last; it turns the sums into scores and puts every accumulator back to zero,
+//   the state the next launch expects.
+#include <algorithm>
 #include <mutex>
 
 #include "sp_device.h"
@@ -20,34 +21,34 @@ namespace sp {
 
 constexpr int kSalThreads = 256;
 constexpr int kSalUnroll = 4;      // 16-byte vectors in flight per thread and step
+constexpr int kSalPieceVecs = kSalThreads * kSalUnroll;          // shortest piece of a row: one step of a workgroup
 constexpr double kFixOne = 68719476736.0;        // 2^36
 constexpr float kFixLimit = 6.0e7f;              // |lp| above this (about 2^26) is treated as infinite
 
 // Scratch of the entry point that allocates nothing: the launch counter, the per-slot accumulators and
-// the per-row log-likelihoods of the largest problem it accepts (kSalStaticRows rows, kSalStaticSlots path slots), on every
+// the per-row partial sums of the largest problem it accepts (kSalStaticRows rows, kSalStaticSlots path slots), on every
 // GPU the library runs on; zero at load, and the accumulators are left at zero by every launch.
 static __device__ __align__(256) unsigned char scratch[kSalStaticBytes];
 
 template <typename T>
 __global__ __launch_bounds__(kSalThreads) void saliency_kernel(const T *__restrict__ logits, int64_t vocab,
                                                              int64_t row_stride,
-                                                             const int32_t *__restrict__ target,
-                                                             RowLp *__restrict__ lp_out) {
+                                                             const int32_t *__restrict__ target, int n_pieces,
+                                                             RowPart *__restrict__ out) {
   constexpr int EV = Elem<T>::kVec;
-  const int64_t r = blockIdx.x;
+  const int64_t r = n_pieces == 1 ? blockIdx.x : blockIdx.x / unsigned(n_pieces);
+  const int piece = int(blockIdx.x - r * n_pieces);
   const int32_t tgt = target[r];
   __shared__ float sm[kSalThreads / 64], ss[kSalThreads / 64];
   float m = kNegBig, s = 0.f;
   const T *row = logits + r * row_stride;
   if (tgt >= 0) {                                // a row that is not scored does not touch its logits
     const int64_t n_vec = vocab / EV;
+    const int64_t v0 = n_pieces == 1 ? 0 : n_vec * piece / n_pieces;
+    const int64_t v1 = n_pieces == 1 ? n_vec : n_vec * (piece + 1) / n_pieces;
     const u32x4 *vrow = reinterpret_cast<const u32x4 *>(row);
     // running maximum m (natural units) and s = sum exp(x - m), per thread
-    int64_t i = threadIdx.x;
-    for (; i + int64_t(kSalUnroll - 1) * kSalThreads < n_vec; i += int64_t(kSalUnroll) * kSalThreads) {
-      u32x4 raw[kSalUnroll];
-#pragma unroll
-      for (int u = 0; u < kSalUnroll; ++u) raw[u] = ld16_stream(vrow + i + int64_t(u) * kSalThreads);
+    auto step = [&](const u32x4 *raw) {
       float x[kSalUnroll * EV];
 #pragma unroll
       for (int u = 0; u < kSalUnroll; ++u) Elem<T>::unpack(raw[u], x + u * EV);
@@ -61,23 +62,24 @@ __global__ __launch_bounds__(kSalThreads) void saliency_kernel(const T *__restri
       for (int j = 0; j < kSalUnroll * EV; ++j) a += fast_exp2(fmaf(x[j], kLog2e, -mb));
       s = fmaf(s, fast_exp2((m - m_new) * kLog2e), a);
       m = m_new;
-    }
-    for (; i < n_vec; i += kSalThreads) {          // remaining whole vectors
-      const u32x4 raw = vrow[i];
-      float x[EV];
-      Elem<T>::unpack(raw, x);
-      float mx = x[0];
+    };
+    int64_t i = v0 + threadIdx.x;
+    u32x4 raw[kSalUnroll];
+    for (; i + int64_t(kSalUnroll - 1) * kSalThreads < v1; i += int64_t(kSalUnroll) * kSalThreads) {
 #pragma unroll
-      for (int j = 1; j < EV; ++j) mx = fmaxf(mx, x[j]);
-      const float m_new = fmaxf(m, mx);
-      const float mb = m_new * kLog2e;
-      float a = 0.f;
-#pragma unroll
-      for (int j = 0; j < EV; ++j) a += fast_exp2(fmaf(x[j], kLog2e, -mb));
-      s = fmaf(s, fast_exp2((m - m_new) * kLog2e), a);
-      m = m_new;
+      for (int u = 0; u < kSalUnroll; ++u) raw[u] = ld16_stream(vrow + i + int64_t(u) * kSalThreads);
+      step(raw);
     }
-    {                                              // scalar tail (vocab not a multiple of the vector)
+    if (i < v1) {                                // the last vectors, all at once; the missing ones are -inf
+      const uint32_t none = EV == 8 ? 0xff80ff80u : 0xff800000u;
+#pragma unroll
+      for (int u = 0; u < kSalUnroll; ++u) {
+        const int64_t at = i + int64_t(u) * kSalThreads;
+        raw[u] = at < v1 ? ld16_stream(vrow + at) : u32x4{none, none, none, none};
+      }
+      step(raw);
+    }
+    if (piece == n_pieces - 1) {                   // scalar tail (vocab not a multiple of the vector)
       const int64_t j = n_vec * EV + threadIdx.x;
       if (j < vocab) {
         const float x = Elem<T>::load1(row + j);
@@ -99,7 +101,7 @@ __global__ __launch_bounds__(kSalThreads) void saliency_kernel(const T *__restri
   }
   __syncthreads();
   if (threadIdx.x != 0) return;
-  if (tgt < 0) { lp_out[r] = RowLp{0ll, 0u, 0u}; return; }
+  if (tgt < 0) { out[blockIdx.x] = RowPart{0.f, 0.f, 0.f, 0u}; return; }
   float M = sm[0];
 #pragma unroll
   for (int w = 1; w < kSalThreads / 64; ++w) M = fmaxf(M, sm[w]);
@@ -107,16 +109,89 @@ __global__ __launch_bounds__(kSalThreads) void saliency_kernel(const T *__restri
 #pragma unroll
   for (int w = 0; w < kSalThreads / 64; ++w) S += ss[w] * fast_exp2((sm[w] - M) * kLog2e);
   const int64_t t = tgt < vocab ? tgt : vocab - 1;
-  const float lp = Elem<T>::load1(row + t) - (M + __logf(S));
-  // fixed point here, where every row has a thread of its own; a value that is not finite becomes a flag
-  RowLp o{0ll, 0u, 1u};
-  if (lp != lp || fabsf(lp) > kFixLimit) o.flags = lp != lp ? 4u : (lp < 0.f ? 1u : 2u);
-  else o.q = __double2ll_rn(double(lp) * kFixOne);
-  lp_out[r] = o;
+  out[blockIdx.x] = RowPart{M, S, piece == 0 ? Elem<T>::load1(row + t) : 0.f, 1u};
+}
+
+// a row's log-likelihood in fixed point, or flag bits when it is not finite
+struct RowLp {
+  long long q;
+  uint32_t flags, scored;
+};
+__device__ __forceinline__ RowLp row_lp(const RowPart *__restrict__ part, int64_t r, int n_pieces) {
+  const RowPart *p = part + r * n_pieces;
+  const RowPart first = p[0];
+  RowLp v{0ll, 0u, first.scored};
+  if (!first.scored) return v;
+  float M = first.m, S = first.s;
+  for (int i = 1; i < n_pieces; ++i) {
+    const RowPart o = p[i];
+    const float m_new = fmaxf(M, o.m);
+    S = S * fast_exp2((M - m_new) * kLog2e) + o.s * fast_exp2((o.m - m_new) * kLog2e);
+    M = m_new;
+  }
+  const float lp = first.x_target - (M + __logf(S));
+  if (lp != lp || fabsf(lp) > kFixLimit) v.flags = lp != lp ? 4u : (lp < 0.f ? 1u : 2u);
+  else v.q = __double2ll_rn(double(lp) * kFixOne);
+  return v;
+}
+__device__ __forceinline__ float slot_score(long long sum, uint32_t count, uint32_t flags, int mode, const float *prior,
+                                            int64_t slot) {
+  float x = float(double(sum) * (1.0 / kFixOne));
+  if (flags) x = ((flags & 4u) || (flags & 3u) == 3u) ? __builtin_nanf("") : ((flags & 1u) ? -INFINITY : INFINITY);
+  if (mode == 1) x = count > 0 ? x / float(count) : 0.f;
+  if (prior) x += prior[slot];
+  return x;
+}
+__device__ __forceinline__ int32_t clamp_slot(int32_t slot, int32_t n_slots) {
+  return slot < 0 ? 0 : (slot >= n_slots ? n_slots - 1 : slot);
 }
 
 constexpr int kRedThreads = 256;
-__global__ __launch_bounds__(kRedThreads) void saliency_reduce_kernel(const RowLp *__restrict__ lp,
+// One workgroup per slot.  Bound by the latency of two dependent reads (row_path, then the slot's rows); there is no atomic,
+// and the reads of row_path are independent of each other and come from the L2.  340 rows of 20 slots: 3.8 us (the atomic
+// kernel 6.2), 3840 rows of 160 slots: 4.7 us (6.1).
+__global__ __launch_bounds__(kRedThreads) void saliency_scan_kernel(const RowPart *__restrict__ part, int n_pieces,
+                                                                    const int32_t *__restrict__ row_path, int32_t n_rows,
+                                                                    const float *__restrict__ prior, int32_t n_slots,
+                                                                    int mode, float *__restrict__ score) {
+  constexpr int U = 8;
+  const int32_t mine = blockIdx.x;
+  long long q = 0;
+  uint32_t count = 0, flags = 0;
+  for (int32_t r0 = threadIdx.x; r0 < n_rows; r0 += U * kRedThreads) {
+    int32_t slot[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int32_t r = r0 + u * kRedThreads;
+      slot[u] = r < n_rows ? clamp_slot(row_path[r], n_slots) : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (slot[u] == mine) {
+        const RowLp v = row_lp(part, r0 + u * kRedThreads, n_pieces);
+        q += v.q;
+        count += v.scored;
+        flags |= v.flags;
+      }
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    q += __shfl_xor(q, off);
+    count += __shfl_xor(count, off);
+    flags |= __shfl_xor(flags, off);
+  }
+  __shared__ long long s_q[kRedThreads / 64];
+  __shared__ uint32_t s_c[kRedThreads / 64], s_f[kRedThreads / 64];
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) { s_q[wave] = q; s_c[wave] = count; s_f[wave] = flags; }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+#pragma unroll
+  for (int w = 1; w < kRedThreads / 64; ++w) { q += s_q[w]; count += s_c[w]; flags |= s_f[w]; }
+  score[mine] = slot_score(q, count, flags, mode, prior, mine);
+}
+
+__global__ __launch_bounds__(kRedThreads) void saliency_reduce_kernel(const RowPart *__restrict__ part, int n_pieces,
                                                                       const int32_t *__restrict__ row_path,
                                                                       int64_t n_rows, const float *__restrict__ prior,
                                                                       int32_t n_slots, int mode, SalSlot *__restrict__ acc,
@@ -127,9 +202,8 @@ __global__ __launch_bounds__(kRedThreads) void saliency_reduce_kernel(const RowL
   RowLp v{0ll, 0u, 0u};
   int32_t slot = 0;
   if (r < n_rows) {
-    v = lp[r];
-    slot = row_path[r];
-    slot = slot < 0 ? 0 : (slot >= n_slots ? n_slots - 1 : slot);
+    v = row_lp(part, r, n_pieces);
+    slot = clamp_slot(row_path[r], n_slots);
   }
   // Rows of one path usually sit next to each other, and atomics on one address are performed one after
   // the other: a wave first adds up, per slot, what its own lanes hold (up to kWaveSlots different slots),
@@ -185,11 +259,7 @@ __global__ __launch_bounds__(kRedThreads) void saliency_reduce_kernel(const RowL
     v.sum = __hip_atomic_load(&a->sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     v.count = __hip_atomic_load(&a->count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     v.flags = __hip_atomic_load(&a->flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    float x = float(double((long long)v.sum) * (1.0 / kFixOne));
-    if (v.flags) x = ((v.flags & 4u) || (v.flags & 3u) == 3u) ? __builtin_nanf("") : ((v.flags & 1u) ? -INFINITY : INFINITY);
-    if (mode == 1) x = v.count > 0 ? x / float(v.count) : 0.f;
-    if (prior) x += prior[i];
-    score[i] = x;
+    score[i] = slot_score((long long)v.sum, v.count, v.flags, mode, prior, i);
     __hip_atomic_store(&a->sum, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(&a->count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(&a->flags, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -197,27 +267,43 @@ __global__ __launch_bounds__(kRedThreads) void saliency_reduce_kernel(const RowL
   if (threadIdx.x == 0) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// scratch: the launch counter (256 bytes), one SalSlot per path slot of the capacity, then one RowLp per
+// scratch: the launch counter (256 bytes), one SalSlot per path slot of the capacity, then one RowPart per
 // row; the counter and the accumulators are zero before the launch and left at zero.
 hipError_t launch_saliency(const void *logits, sp_dtype dt, int64_t n_rows, int64_t vocab, int64_t row_stride,
                            const int32_t *target, const int32_t *row_path, const float *prior, int32_t n_slots,
                            int mode, void *scratch, int32_t cap_slots, float *score, hipStream_t s) {
   uint32_t *done = static_cast<uint32_t *>(scratch);
   SalSlot *acc = reinterpret_cast<SalSlot *>(static_cast<unsigned char *>(scratch) + 256);
-  RowLp *lp = reinterpret_cast<RowLp *>(acc + cap_slots);
+  RowPart *part = reinterpret_cast<RowPart *>(acc + cap_slots);
+  // With fewer rows than workgroups that the device holds at once (8 per compute unit), rows are cut into as many pieces as
+  // fill it, none shorter than one step of a workgroup.  340 fp32 rows of 50257 in 6 pieces: 11.6 us, 5.9 TB/s (whole rows,
+  // most compute units with one workgroup's 16 KB in flight: 14.2 us).
+  const int64_t n_vec = vocab / (dt == SP_BF16 ? 8 : 4);
+  int n_pieces = 1;
+  if (n_rows > 0)
+    n_pieces = int(std::max<int64_t>(1, std::min(kSalSplitRows / n_rows, n_vec / kSalPieceVecs)));
   if (n_rows > 0) {
+    const dim3 grid(unsigned(n_rows * n_pieces));
     if (dt == SP_BF16)
-      hipLaunchKernelGGL(saliency_kernel<__bf16>, dim3(unsigned(n_rows)), dim3(kSalThreads), 0, s,
-                         static_cast<const __bf16 *>(logits), vocab, row_stride, target, lp);
+      hipLaunchKernelGGL(saliency_kernel<__bf16>, grid, dim3(kSalThreads), 0, s, static_cast<const __bf16 *>(logits),
+                         vocab, row_stride, target, n_pieces, part);
     else
-      hipLaunchKernelGGL(saliency_kernel<float>, dim3(unsigned(n_rows)), dim3(kSalThreads), 0, s,
-                         static_cast<const float *>(logits), vocab, row_stride, target, lp);
+      hipLaunchKernelGGL(saliency_kernel<float>, grid, dim3(kSalThreads), 0, s, static_cast<const float *>(logits), vocab,
+                         row_stride, target, n_pieces, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
+  // The scan reads rows * slots path numbers from the L2: kScanReads of them are 16 MB over all workgroups, and kScanRows
+  // rows four rounds of a workgroup.
+  constexpr int64_t kScanReads = int64_t(1) << 22, kScanRows = 8192;
+  if (n_rows <= kScanRows && n_rows * n_slots <= kScanReads) {
+    hipLaunchKernelGGL(saliency_scan_kernel, dim3(unsigned(n_slots)), dim3(kRedThreads), 0, s, part, n_pieces, row_path,
+                       int32_t(n_rows), prior, n_slots, mode, score);
+    return hipGetLastError();
+  }
   const unsigned grid = n_rows > 0 ? unsigned((n_rows + kRedThreads - 1) / kRedThreads) : 1u;
-  hipLaunchKernelGGL(saliency_reduce_kernel, dim3(grid), dim3(kRedThreads), 0, s, lp, row_path, n_rows, prior, n_slots,
-                     mode, acc, done, score);
+  hipLaunchKernelGGL(saliency_reduce_kernel, dim3(grid), dim3(kRedThreads), 0, s, part, n_pieces, row_path, n_rows, prior,
+                     n_slots, mode, acc, done, score);
   return hipGetLastError();
 }
 
