@@ -28,6 +28,8 @@
 // and the exponentiated scores are already in the B-operand layout of the second product: the
 // k-slots of that MFMA are simply bound to the keys this lane holds, and the V fragment is read
 // with the same key order.
+#include <type_traits>
+
 #include "sp_device.h"
 #include "sp_internal.h"
 
@@ -74,7 +76,10 @@ __device__ __forceinline__ float sload_f32(const float *p) {
   return v;
 }
 
-template <int D, int HPW, int NW, bool BIAS>
+// MANY: some row group of the plan has more than one ancestor range.  Plans without such a group take a kernel that does not
+// know ranges at all: the search below costs scalar registers that the stage loop does not have to spare (with it compiled
+// in, plans of one range lose 1-2 %).
+template <int D, int HPW, int NW, bool BIAS, bool MANY>
 __global__ __launch_bounds__(64 * NW, 2) void prefill_bf16_kernel(PlanDev pd, const __bf16 *__restrict__ Q,
                                                                   const __bf16 *__restrict__ K,
                                                                   const __bf16 *__restrict__ V,
@@ -103,7 +108,9 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_bf16_kernel(PlanDev pd, co
   __shared__ __attribute__((aligned(256))) float Ps[2][BK < 64 ? 64 : BK];   // key positions (bias); one 64-lane DMA each
   __shared__ __attribute__((aligned(256))) float Pq[64];                     // positions of the rows of the Q tile in flight
   __shared__ __attribute__((aligned(16))) WorkItem s_items[kItemBatch];
-  __shared__ KeyRange s_ranges[kItemBatch][kRangeCache];       // first ancestor ranges of each staged item
+  // first ancestor ranges of each staged item as {delta, end}: virtual keys from the end of the entry before up to `end`
+  // are the tokens delta + key; entries behind the last range stand for the own run
+  __shared__ __attribute__((aligned(8))) int2 s_ranges[MANY ? kItemBatch : 1][kRangeCache];
   auto fK = [](int row) { return (row / RPC) % CPR; };
   auto fV = [](int row) { return 4 * ((row / RPC) % (CPR / 4)); };
 
@@ -165,13 +172,13 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_bf16_kernel(PlanDev pd, co
   auto map_tok = [&](const Item &w, int local, int vk) -> int {
     vk = min(vk, w.anc_keys + w.row0 + w.n_rows - 1);           // past the end: re-read the last key (masked)
     if (vk >= w.anc_keys) return w.tok_start + (vk - w.anc_keys);
-    if (w.n_ranges == 1) return w.r0_start + vk;
+    if (!MANY || w.n_ranges == 1) return w.r0_start + vk;
     int tok = 0;
     if (w.n_ranges <= kRangeCache) {                            // the LDS copy, else the plan's table
       for (int r = 0; r < w.n_ranges; ++r) {
-        const int2 kr = *reinterpret_cast<const int2 *>(&s_ranges[local][r]);
-        if (vk >= 0 && vk < kr.y) tok = kr.x + vk;
-        vk -= kr.y;
+        const int2 kr = s_ranges[local][r];
+        tok = kr.x + vk;
+        if (vk < kr.y) break;
       }
     } else {
       for (int r = 0; r < w.n_ranges; ++r) {
@@ -207,24 +214,35 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_bf16_kernel(PlanDev pd, co
       // A stage whose BK keys are consecutive tokens (inside the own run and not past its end, or
       // inside a single ancestor range) needs no per-lane token lookup.
       const int vk0 = st * BK;
-      int tok0 = -1;
+      int tok0 = -1, end = 0, delta = 0, next_end = 0, next_delta = 0;
       if (vk0 >= w.anc_keys) {
         if (vk0 + BK <= w.anc_keys + w.row0 + w.n_rows) tok0 = w.tok_start + (vk0 - w.anc_keys);
       } else if (vk0 + BK <= w.anc_keys) {
-        if (w.n_ranges == 1) {
+        if (!MANY || w.n_ranges == 1) {
           tok0 = w.r0_start + vk0;
         } else if (w.n_ranges <= kRangeCache) {
-          // several ancestor ranges (cached paths, chains of kept documents): find the one that
-          // holds the whole stage, if any, in the LDS copy of the ranges
-          int acc = 0;
-          for (int r = 0; r < w.n_ranges; ++r) {
-            const int2 kr = *reinterpret_cast<const int2 *>(&s_ranges[local][r]);
-            const int start = __builtin_amdgcn_readfirstlane(kr.x), len = __builtin_amdgcn_readfirstlane(kr.y);
-            if (vk0 >= acc && vk0 + BK <= acc + len) tok0 = start + (vk0 - acc);
-            acc += len;
+          // several ancestor ranges (cached paths, chains of kept documents): one lane per range finds the one that holds
+          // the stage's first key.  (A loop over the ranges, one LDS round trip each, cost 12 % of a launch behind a
+          // chain of four documents: 414 us, now 364.)
+          const int2 kr = s_ranges[local][lane % kRangeCache];
+          const int r = __builtin_ctz(uint32_t(__ballot(vk0 < kr.y)) | 1u << (kRangeCache - 1));
+          end = __builtin_amdgcn_readlane(kr.y, r);
+          delta = __builtin_amdgcn_readlane(kr.x, r);
+          if (vk0 + BK <= end) {
+            tok0 = delta + vk0;
+          } else if (r + 1 < kRangeCache) {
+            // the stage reaches into the next range or, behind the last one, into the own run
+            next_end = __builtin_amdgcn_readlane(kr.y, r + 1);
+            next_delta = __builtin_amdgcn_readlane(kr.x, r + 1);
           }
         }
       }
+      const bool two = MANY && next_end >= vk0 + BK;                // two ranges hold the stage: no search per lane
+      auto stage_tok = [&](int vk) -> int {
+        if (!two) return map_tok(w, local, vk);
+        vk = min(vk, w.anc_keys + w.row0 + w.n_rows - 1);     // past the end, as in map_tok
+        return (vk < end ? delta : next_delta) + vk;
+      };
       const uint64_t hoff = (uint64_t)(uint32_t)w.kv_head * kv_hs * 2;
       if (tok0 >= 0) {
         const uint64_t o0 = (uint64_t)(uint32_t)(tok0 + rbase) * kv_ts * 2 + hoff;
@@ -235,11 +253,11 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_bf16_kernel(PlanDev pd, co
       } else {
 #pragma unroll
         for (int m = 0; m < NDMA; ++m) {
-          const int tok = map_tok(w, local, vk0 + rbase + RG * m + drow);
+          const int tok = stage_tok(vk0 + rbase + RG * m + drow);
           dma16(KVb + ((uint64_t)(uint32_t)tok * kv_ts * 2 + hoff + xkv[m]), lds + m * (RG * ROWB));
         }
         if (BIAS && wave == 0)
-          dma4(pd.tok_pos + map_tok(w, local, vk0 + min(lane, BK - 1)), ps_base + slot * kPsSlotB);
+          dma4(pd.tok_pos + stage_tok(vk0 + min(lane, BK - 1)), ps_base + slot * kPsSlotB);
       }
     }
   };
@@ -284,10 +302,19 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_bf16_kernel(PlanDev pd, co
 
     issue(cur, 0, -1, 0);
     // the items' ancestor ranges, fetched under the first Q tile (items with one range carry it)
-    for (int i = tid; i < (it_end - it) * kRangeCache; i += T) {
+    for (int i = tid; MANY && i < (it_end - it) * kRangeCache; i += T) {
       const int li = i / kRangeCache, r = i % kRangeCache;
       const int n_rng = s_items[li].n_ranges;
-      if (n_rng > 1 && r < n_rng) s_ranges[li][r] = pd.ranges[s_items[li].range_off + r];
+      if (n_rng > 1) {
+        int2 e = {s_items[li].tok_start - s_items[li].anc_keys, 0x7fffffff};
+        if (r < n_rng) {
+          int begin = 0;
+          for (int j = 0; j < r; ++j) begin += pd.ranges[s_items[li].range_off + j].len;
+          const KeyRange kr = pd.ranges[s_items[li].range_off + r];
+          e = {kr.tok_start - begin, begin + kr.len};
+        }
+        s_ranges[li][r] = e;
+      }
     }
     land_and_sync(0);
 
@@ -458,12 +485,14 @@ static hipError_t launch_hpw(const sp_plan *plan, const PrefillArgs &a, hipStrea
   __bf16 *O = static_cast<__bf16 *>(a.O);
   const uint32_t qts = uint32_t(a.q_tok_stride), qhs = uint32_t(a.q_head_stride), kts = uint32_t(a.kv_tok_stride),
                  khs = uint32_t(a.kv_head_stride);
-  if (plan->has_slopes)
-    hipLaunchKernelGGL((prefill_bf16_kernel<D, HPW, NW, true>), grid, dim3(64 * NW), 0, s, plan->dev, Q, K, V, O,
-                       qts, qhs, kts, khs, a.scale);
-  else
-    hipLaunchKernelGGL((prefill_bf16_kernel<D, HPW, NW, false>), grid, dim3(64 * NW), 0, s, plan->dev, Q, K, V, O,
-                       qts, qhs, kts, khs, a.scale);
+  auto launch = [&](auto bias, auto many) {
+    hipLaunchKernelGGL((prefill_bf16_kernel<D, HPW, NW, decltype(bias)::value, decltype(many)::value>), grid,
+                       dim3(64 * NW), 0, s, plan->dev, Q, K, V, O, qts, qhs, kts, khs, a.scale);
+  };
+  auto pick = [&](auto bias) {
+    if (plan->max_ranges > 1) launch(bias, std::true_type{}); else launch(bias, std::false_type{});
+  };
+  if (plan->has_slopes) pick(std::true_type{}); else pick(std::false_type{});
   return hipGetLastError();
 }
 
