@@ -360,11 +360,9 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_bf16_kernel(PlanDev pd, co
           pos_q = Pq[my_row];
         }
       } else {
-#pragma unroll
-        for (int sub = 0; sub < BK / 32; ++sub) {
+        // one block of 32 keys
+        auto block = [&](const int sub) {
           const int vk0 = st * BK + 32 * sub;
-          if (!active || vk0 > wave_last) continue;           // block entirely above this wave's diagonal
-
           f32x16 s;
 #pragma unroll
           for (int i = 0; i < 16; ++i) s[i] = 0.f;
@@ -426,7 +424,11 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_bf16_kernel(PlanDev pd, co
               o[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[mm], o[c], 0, 0, 0);
             }
           }
-        }
+        };
+        // blocks entirely above this wave's diagonal are not computed
+#pragma unroll
+        for (int sub = 0; sub < BK / 32; ++sub)
+          if (active && st * BK + 32 * sub <= wave_last) block(sub);
 
         if (last_stage) {
           // Epilogue of the item.  O^T sits in registers one query row per lane; it is transposed
