@@ -159,15 +159,15 @@ class Context:
 
     # -- a1 ------------------------------------------------------------------------------
     def sp_forkjoin_prefill(self, plan: "Plan", Q, K, V, O, softmax_scale: float):
-        if not (Q.stride(-1) == K.stride(-1) == V.stride(-1) == O.stride(-1) == 1):
+        qs, ks, vs, os_ = Q.stride(), K.stride(), V.stride(), O.stride()
+        if not (qs[-1] == ks[-1] == vs[-1] == os_[-1] == 1):
             raise ValueError("innermost stride must be 1")
-        if O.stride(0) != Q.stride(0) or O.stride(1) != Q.stride(1) or K.stride() != V.stride():
+        if os_[0] != qs[0] or os_[1] != qs[1] or ks != vs:
             raise ValueError("O must share Q's strides and V must share K's strides")
         if _dtype_code(Q) != plan.dtype:
             raise ValueError("tensor dtype does not match the plan")
         self._check(lib().sp_forkjoin_prefill(self._h, plan._h, _dev(Q, "Q"), _dev(K, "K"), _dev(V, "V"),
-                                              _dev(O, "O"), Q.stride(0), Q.stride(1), K.stride(0), K.stride(1),
-                                              float(softmax_scale)))
+                                              _dev(O, "O"), qs[0], qs[1], ks[0], ks[1], float(softmax_scale)))
         return O
 
     # -- a2 ------------------------------------------------------------------------------
@@ -197,18 +197,29 @@ class Context:
     def sp_pruned_decode(self, plan: "Plan", kept, k: int, K_prefill, V_prefill, K_resp, V_resp, resp_capacity: int,
                          q_new, k_new, v_new, o_out, softmax_scale: float, resp_len=None, resp_len_add: int = 0,
                          pos_resp=None, new_pos=None):
-        if K_prefill.stride() != V_prefill.stride() or K_prefill.stride(-1) != 1:
+        # Called once per token and layer: this function's own time is what a small step waits for, so each property of
+        # a tensor is asked for once and the checks are one expression each, spelled out only to name what failed.
+        ks = K_prefill.stride()
+        if ks != V_prefill.stride() or ks[-1] != 1:
             raise ValueError("K_prefill and V_prefill must share strides, inner stride 1")
-        for t, n in ((K_resp, "K_resp"), (V_resp, "V_resp"), (q_new, "q_new"), (k_new, "k_new"), (v_new, "v_new"),
-                     (o_out, "o_out")):
-            if not t.is_contiguous():
-                raise ValueError("%s must be contiguous" % n)
-        self._check(lib().sp_pruned_decode(self._h, plan._h, _dev(kept, "kept"), int(k), _dev(K_prefill, "K_prefill"),
-                                           _dev(V_prefill, "V_prefill"), K_prefill.stride(0), K_prefill.stride(1),
-                                           _dev(K_resp, "K_resp"), _dev(V_resp, "V_resp"), _dev(pos_resp, "pos_resp"),
-                                           int(resp_capacity), _dev(resp_len, "resp_len"), int(resp_len_add),
-                                           _dev(new_pos, "new_pos"), _dev(q_new, "q_new"), _dev(k_new, "k_new"),
-                                           _dev(v_new, "v_new"), _dev(o_out, "o_out"), float(softmax_scale)))
+        if not (K_resp.is_contiguous() and V_resp.is_contiguous() and q_new.is_contiguous() and k_new.is_contiguous()
+                and v_new.is_contiguous() and o_out.is_contiguous()):
+            for t, n in ((K_resp, "K_resp"), (V_resp, "V_resp"), (q_new, "q_new"), (k_new, "k_new"), (v_new, "v_new"),
+                         (o_out, "o_out")):
+                if not t.is_contiguous():
+                    raise ValueError("%s must be contiguous" % n)
+        if not (K_prefill.is_cuda and V_prefill.is_cuda and K_resp.is_cuda and V_resp.is_cuda and q_new.is_cuda
+                and k_new.is_cuda and v_new.is_cuda and o_out.is_cuda):
+            for t, n in ((K_prefill, "K_prefill"), (V_prefill, "V_prefill"), (K_resp, "K_resp"), (V_resp, "V_resp"),
+                         (q_new, "q_new"), (k_new, "k_new"), (v_new, "v_new"), (o_out, "o_out")):
+                _dev(t, n)
+        st = lib().sp_pruned_decode(self._h, plan._h, _dev(kept, "kept"), int(k), K_prefill.data_ptr(),
+                                    V_prefill.data_ptr(), ks[0], ks[1], K_resp.data_ptr(), V_resp.data_ptr(),
+                                    _dev(pos_resp, "pos_resp"), int(resp_capacity), _dev(resp_len, "resp_len"),
+                                    int(resp_len_add), _dev(new_pos, "new_pos"), q_new.data_ptr(), k_new.data_ptr(),
+                                    v_new.data_ptr(), o_out.data_ptr(), float(softmax_scale))
+        if st != 0:
+            self._check(st)
         return o_out
 
 
