@@ -348,7 +348,8 @@ __global__ __launch_bounds__(kDecThreads, GC == 1 ? 4 : 2) void decode_kernel(Pl
       if (t0 + BATCH <= min(c1, key1)) {         // consecutive tokens of one range (nearly every batch)
         const int64_t stride = uniform64(tab.stride[i0]), off = (t0 - c0 + kgw) * stride + sub * 16;
         const char *kp = tab.k[i0] + off, *vp = tab.v[i0] + off;
-        // non-temporal: every row is read once (64 prompts of 32 heads, 430 keys: 103.1 -> 93.0 us, 5.8 TB/s)
+        // non-temporal: a row is read once, or once per chunk of query heads (64 prompts of 32 heads, 430 keys: 103.1 ->
+        // 93.0 us, 5.8 TB/s)
 #pragma unroll
         for (int u = 0; u < kDecUnroll; ++u) {
           bt.kraw[u] = ld16_stream(kp + u * KPI * stride);

@@ -15,11 +15,12 @@
 // are loaded straight from memory into registers, V under the first product, the next K under the second, and no wave
 // waits for another.  16 rows per wave and not 32: a masked half of a diagonal tile and an unfilled last tile cost half as
 // much, and the waves are short enough for the last of them to end together.  Sums are kept in short chains that are then
-// added up: one chain of D products (and one of all keys for O) has twice the error of the vector kernel that was here
-// before, the short ones have 0.80 to 0.99 of its error against 64 bits.
+// added up: one chain of D products (and one of all keys for O) has 1.75 times the error of one wave per row in vector
+// arithmetic, the short ones have 0.80 to 0.99 of it (against 64 bits, four shapes).
 // Measured, one prompt of 20 documents of 64-220 tokens, 32 heads of 128 dims (9.9 GFLOP): 712 us with one wave per row in
-// vector arithmetic, 161 us now (in a profiled run 176; there 194 us with the waves of an item in one workgroup (it keeps its place until its longest
-// wave ends, and 209 us with K and V staged through LDS for the four waves of an item).
+// vector arithmetic, 161 us now.  In a profiled run, where it takes 176: 194 us with the waves of an item in one workgroup
+// (it keeps its place until its longest wave ends), 209 us with K and V staged through LDS for the four waves of an item.
+// Without the early K loads, at three waves per SIMD: 183 us where this one took 164.
 #include "sp_device.h"
 #include "sp_internal.h"
 
