@@ -359,11 +359,13 @@ __global__ __launch_bounds__(kDecThreads, GC == 1 ? 4 : 2) void decode_kernel(Pl
       } else {
 #pragma unroll
         for (int u = 0; u < kDecUnroll; ++u) {
-          const int vk = min(t0 + kgw + u * KPI, key1 - 1);      // lanes past the end re-read the last key
+          // lanes past the end re-read the last key's K and take zeros for V, whose weight is zero: 0 * inf is not 0
+          const int mine = t0 + kgw + u * KPI, vk = min(mine, key1 - 1);
           const int i = find.from(i0, vk);
           const int64_t off = int64_t(vk - tab.cum[i]) * tab.stride[i] + sub * 16;
           bt.kraw[u] = ld16_stream(tab.k[i] + off);
-          bt.vraw[u] = ld16_stream(tab.v[i] + off);
+          bt.vraw[u] = u32x4{0, 0, 0, 0};
+          if (mine < key1) bt.vraw[u] = ld16_stream(tab.v[i] + off);
           bt.pk[u] = BIAS ? tab.pos[i][vk - tab.cum[i]] : 0.f;
         }
       }
@@ -547,8 +549,12 @@ __global__ __launch_bounds__(kDecThreads) void decode_gqa_kernel(PlanDev pd, Dec
           for (int j = 0; j < NJ; ++j) kf[u][j] = *reinterpret_cast<const bf16x8 *>(kp + 64 * j);
 #pragma unroll
           for (int i = 0; i < NV; ++i) {
-            const int vk = min(t0 + 16 * u + 4 * g + (LPR == 8 ? 2 * i + vhalf : i), key1 - 1), iv = find.from(i0, vk);
-            vf[u][i] = ld16_stream(tab.v[iv] + int64_t(vk - tab.cum[iv]) * tab.stride[iv] + vc * 16);
+            const int vk = t0 + 16 * u + 4 * g + (LPR == 8 ? 2 * i + vhalf : i);
+            vf[u][i] = u32x4{0, 0, 0, 0};                          // no key, no V: its weight is zero, and 0 * inf is not
+            if (vk < key1) {
+              const int iv = find.from(i0, vk);
+              vf[u][i] = ld16_stream(tab.v[iv] + int64_t(vk - tab.cum[iv]) * tab.stride[iv] + vc * 16);
+            }
           }
           if (BIAS)
 #pragma unroll
