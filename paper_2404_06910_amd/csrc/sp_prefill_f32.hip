@@ -188,9 +188,10 @@ __global__ __launch_bounds__(64, 2) void prefill_f32_kernel(PlanDev pd, const fl
       if (diag && vk0 + 4 * quad + r > my_limit) t[r] = -INFINITY;
     }
     const float mx = quad_max(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3])));
-    // the reference maximum may lag by up to 8 (a factor of 256 in p and in both sums): nothing to rescale then
-    if (__any(mx > m + 8.f)) {
-      const float m_new = fmaxf(m, mx), alpha = fast_exp2(m - m_new);
+    // The reference is set 8 above the maximum and stays until a score passes it, so that most steps have nothing to
+    // rescale; p (2^-8 at the maximum) and both sums never exceed what a reference at the maximum gives.
+    if (__any(mx > m)) {
+      const float m_new = mx > m ? mx + 8.f : m, alpha = fast_exp2(m - m_new);
       m = m_new;
       l *= alpha;
 #pragma unroll
