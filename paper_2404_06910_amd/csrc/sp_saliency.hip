@@ -296,9 +296,10 @@ hipError_t launch_saliency(const void *logits, sp_dtype dt, int64_t n_rows, int6
     if (e != hipSuccess) return e;
   }
   // The scan reads rows * slots path numbers from the L2: kScanReads of them are 16 MB over all workgroups, and kScanRows
-  // rows four rounds of a workgroup.
+  // rows four rounds of a workgroup.  It launches a workgroup per slot, whatever the rows, so kScanReads bounds the slots
+  // as well (a launch ends at 2^24 workgroups).
   constexpr int64_t kScanReads = int64_t(1) << 22, kScanRows = 8192;
-  if (n_rows <= kScanRows && n_rows * n_slots <= kScanReads) {
+  if (n_rows <= kScanRows && std::max<int64_t>(n_rows, 1) * n_slots <= kScanReads) {
     hipLaunchKernelGGL(saliency_scan_kernel, dim3(unsigned(n_slots)), dim3(kRedThreads), 0, s, part, n_pieces, row_path,
                        int32_t(n_rows), prior, n_slots, mode, score);
     return hipGetLastError();
