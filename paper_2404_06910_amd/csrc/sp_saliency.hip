@@ -13,6 +13,7 @@
 //   the state the next launch expects.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "sp_device.h"
 #include "sp_internal.h"
@@ -34,7 +35,7 @@ template <typename T>
 __global__ __launch_bounds__(kSalThreads) void saliency_kernel(const T *__restrict__ logits, int64_t vocab,
                                                              int64_t row_stride,
                                                              const int32_t *__restrict__ target, int n_pieces,
-                                                             RowPart *__restrict__ out) {
+                                                             bool tail_at_once, RowPart *__restrict__ out) {
   constexpr int EV = Elem<T>::kVec;
   const int64_t r = n_pieces == 1 ? blockIdx.x : blockIdx.x / unsigned(n_pieces);
   const int piece = int(blockIdx.x - r * n_pieces);
@@ -48,36 +49,54 @@ __global__ __launch_bounds__(kSalThreads) void saliency_kernel(const T *__restri
     const int64_t v1 = n_pieces == 1 ? n_vec : n_vec * (piece + 1) / n_pieces;
     const u32x4 *vrow = reinterpret_cast<const u32x4 *>(row);
     // running maximum m (natural units) and s = sum exp(x - m), per thread
-    auto step = [&](const u32x4 *raw) {
-      float x[kSalUnroll * EV];
+    auto step = [&](const u32x4 *raw, auto vectors) {
+      constexpr int N = decltype(vectors)::value;
+      float x[N * EV];
 #pragma unroll
-      for (int u = 0; u < kSalUnroll; ++u) Elem<T>::unpack(raw[u], x + u * EV);
+      for (int u = 0; u < N; ++u) Elem<T>::unpack(raw[u], x + u * EV);
       float mx = x[0];
 #pragma unroll
-      for (int j = 1; j < kSalUnroll * EV; ++j) mx = fmaxf(mx, x[j]);
+      for (int j = 1; j < N * EV; ++j) mx = fmaxf(mx, x[j]);
       const float m_new = fmaxf(m, mx);
       const float mb = m_new * kLog2e;
       float a = 0.f;
 #pragma unroll
-      for (int j = 0; j < kSalUnroll * EV; ++j) a += fast_exp2(fmaf(x[j], kLog2e, -mb));
+      for (int j = 0; j < N * EV; ++j) a += fast_exp2(fmaf(x[j], kLog2e, -mb));
       s = fmaf(s, fast_exp2((m - m_new) * kLog2e), a);
       m = m_new;
     };
     int64_t i = v0 + threadIdx.x;
     u32x4 raw[kSalUnroll];
-    for (; i + int64_t(kSalUnroll - 1) * kSalThreads < v1; i += int64_t(kSalUnroll) * kSalThreads) {
+    // whole steps: as many as every lane has, or as many as this lane has
+    const int64_t steps_end = tail_at_once ? v1 - (kSalThreads - 1) + threadIdx.x : v1;
+    for (; i + (kSalUnroll - 1) * kSalThreads < steps_end; i += kSalPieceVecs) {
 #pragma unroll
-      for (int u = 0; u < kSalUnroll; ++u) raw[u] = ld16_stream(vrow + i + int64_t(u) * kSalThreads);
-      step(raw);
+      for (int u = 0; u < kSalUnroll; ++u) raw[u] = ld16_stream(vrow + i + u * kSalThreads);
+      step(raw, std::integral_constant<int, kSalUnroll>{});
     }
-    if (i < v1) {                                // the last vectors, all at once; the missing ones are -inf
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (tail_at_once) {
+      // A wave requests all that it still has together; where a lane has no vector it takes -inf.
+      const int left = __builtin_amdgcn_readfirstlane(int(v1 - i));
       const uint32_t none = EV == 8 ? 0xff80ff80u : 0xff800000u;
+      auto last = [&](auto vectors) {
+        constexpr int N = decltype(vectors)::value;
 #pragma unroll
-      for (int u = 0; u < kSalUnroll; ++u) {
-        const int64_t at = i + int64_t(u) * kSalThreads;
-        raw[u] = at < v1 ? ld16_stream(vrow + at) : u32x4{none, none, none, none};
+        for (int u = 0; u < N; ++u) {
+          raw[u] = u32x4{none, none, none, none};
+          if (lane + u * kSalThreads < left) raw[u] = ld16_stream(vrow + i + u * kSalThreads);
+        }
+        step(raw, vectors);
+      };
+      if (left > 3 * kSalThreads) last(std::integral_constant<int, 4>{});
+      else if (left > 2 * kSalThreads) last(std::integral_constant<int, 3>{});
+      else if (left > kSalThreads) last(std::integral_constant<int, 2>{});
+      else if (left > 0) last(std::integral_constant<int, 1>{});
+    } else {
+      for (; i < v1; i += kSalThreads) {
+        raw[0] = ld16(vrow + i);
+        step(raw, std::integral_constant<int, 1>{});
       }
-      step(raw);
     }
     if (piece == n_pieces - 1) {                   // scalar tail (vocab not a multiple of the vector)
       const int64_t j = n_vec * EV + threadIdx.x;
@@ -96,8 +115,7 @@ __global__ __launch_bounds__(kSalThreads) void saliency_kernel(const T *__restri
       s = s * fast_exp2((m - m_new) * kLog2e) + s_o * fast_exp2((m_o - m_new) * kLog2e);
       m = m_new;
     }
-    const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) { sm[wave] = m; ss[wave] = s; }
+    if (lane == 0) { sm[wave] = m; ss[wave] = s; }
   }
   __syncthreads();
   if (threadIdx.x != 0) return;
@@ -147,6 +165,7 @@ __device__ __forceinline__ int32_t clamp_slot(int32_t slot, int32_t n_slots) {
 }
 
 constexpr int kRedThreads = 256;
+constexpr int64_t kScanReads = int64_t(1) << 22, kScanRows = 4096, kScanRowsManySlots = 7168, kManySlots = 500;
 // One workgroup per slot.  Bound by the latency of two dependent reads (row_path, then the slot's rows); there is no atomic,
 // and the reads of row_path are independent of each other and come from the L2.  340 rows of 20 slots: 3.8 us (the atomic
 // kernel 6.2), 3840 rows of 160 slots: 4.7 us (6.1).
@@ -284,22 +303,28 @@ hipError_t launch_saliency(const void *logits, sp_dtype dt, int64_t n_rows, int6
   int n_pieces = 1;
   if (n_rows > 0)
     n_pieces = int(std::max<int64_t>(1, std::min(kSalSplitRows / n_rows, n_vec / kSalPieceVecs)));
+  // The last vectors of a row (or piece) at once, except where thousands of rows keep every compute unit busy with others:
+  // us a call, all at once / one after the other, 4000 bf16 rows of 6200 17.6 / 19.8, 4097 fp32 rows of 32000 83.8 / 86.5;
+  // 5000 bf16 rows of 128256 203.8 / 201.8, 20000 of 32000 197.5 / 192.9, 20000 of 2048 31.4 / 28.5.
+  const bool tail_at_once = n_rows <= kScanRows;
   if (n_rows > 0) {
     const dim3 grid(unsigned(n_rows * n_pieces));
     if (dt == SP_BF16)
       hipLaunchKernelGGL(saliency_kernel<__bf16>, grid, dim3(kSalThreads), 0, s, static_cast<const __bf16 *>(logits),
-                         vocab, row_stride, target, n_pieces, part);
+                         vocab, row_stride, target, n_pieces, tail_at_once, part);
     else
       hipLaunchKernelGGL(saliency_kernel<float>, grid, dim3(kSalThreads), 0, s, static_cast<const float *>(logits), vocab,
-                         row_stride, target, n_pieces, part);
+                         row_stride, target, n_pieces, tail_at_once, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  // The scan reads rows * slots path numbers from the L2: kScanReads of them are 16 MB over all workgroups, and kScanRows
-  // rows four rounds of a workgroup.  It launches a workgroup per slot, whatever the rows, so kScanReads bounds the slots
-  // as well (a launch ends at 2^24 workgroups).
-  constexpr int64_t kScanReads = int64_t(1) << 22, kScanRows = 8192;
-  if (n_rows <= kScanRows && std::max<int64_t>(n_rows, 1) * n_slots <= kScanReads) {
+  // The scan reads rows * slots path numbers from the L2, and a thread of it every 256th row.  Measured, us a call of 512
+  // fp32 logits a row, scan / atomics: 3000 rows of 20 slots 9.2 / 9.4; 4096 rows of 500 slots 10.5 / 14.6; 4097 of 20
+  // 11.0 / 10.3, of 500 11.2 / 15.2; 6500 of 600 14.9 / 16.7, of 20 14.4 / 12.4; 8192 of 512 16.6 / 16.6, of 100 16.2 / 14.4.
+  // kScanReads are 16 MB over all workgroups.  The scan launches a workgroup per slot, whatever the rows, so it bounds the
+  // slots as well (a launch ends at 2^24 workgroups).
+  if (n_rows <= (n_slots >= kManySlots ? kScanRowsManySlots : kScanRows) &&
+      std::max<int64_t>(n_rows, 1) * n_slots <= kScanReads) {
     hipLaunchKernelGGL(saliency_scan_kernel, dim3(unsigned(n_slots)), dim3(kRedThreads), 0, s, part, n_pieces, row_path,
                        int32_t(n_rows), prior, n_slots, mode, score);
     return hipGetLastError();

@@ -71,10 +71,12 @@ def test_values_that_are_not_finite_in_any_piece(ctx, dtype):
     assert got[6] == 0.0
 
 
-def test_scan_and_atomic_sums_agree_bit_for_bit(ctx):
-    """8192 rows are the most that the scan takes; one more row, without a target, goes through the atomics."""
+@pytest.mark.parametrize("rows,n_slots", [(4096, 300), (7168, 512)])
+def test_scan_and_atomic_sums_agree_bit_for_bit(ctx, rows, n_slots):
+    """The most rows that the scan takes (more where there are many slots); one more row, without a target, goes through
+    the atomics."""
     rng = np.random.default_rng(9)
-    rows, vocab, n_slots = 8192, 40, 300
+    vocab = 40
     x = rng.normal(0, 3, (rows + 1, vocab)).astype(np.float32)
     target = rng.integers(0, vocab, rows + 1).astype(np.int32)
     target[rng.integers(0, rows, 500)] = -1
