@@ -127,6 +127,9 @@ __device__ __forceinline__ void build_key_table(const PlanDev &pd, const DecodeD
   __syncthreads();
 }
 
+template <bool STREAM>
+__device__ __forceinline__ u32x4 ld16_kv(const void *p) { return STREAM ? ld16_stream(p) : ld16(p); }
+
 // Range of a key (vk < n_total, so every search ends at the latest on the new token's range).  Every lane keeps one
 // running count, so that the range of a wave-uniform key is one comparison and a bit count; walking the counts in LDS
 // instead costs a dependent LDS read per range, which a piece of a few dozen keys feels (1 us of 4).
@@ -294,7 +297,10 @@ __device__ __forceinline__ void run_pieces(const PlanDev &pd, const DecodeDev &a
   }
 }
 
-template <typename T, int D, int GC, bool BIAS>
+// STREAM: a workgroup reads its K and V rows alone (one chunk of query heads per KV head), so they are read non-temporally
+// (64 prompts of 32 heads, 430 keys: 103.1 -> 93.0 us, 5.8 TB/s).  Where several chunks read the same rows, cached loads let
+// the later ones find them in the caches (64 fp32 prompts of 40/4 heads, five chunks: non-temporally 100.7, cached 77.7 us).
+template <typename T, int D, int GC, bool BIAS, bool STREAM>
 __global__ __launch_bounds__(kDecThreads, GC == 1 ? 4 : 2) void decode_kernel(PlanDev pd, DecodeDev a) {
   constexpr int EV = Elem<T>::kVec;       // elements per 16-byte lane load
   constexpr int LPK = D / EV;             // lanes per key row
@@ -348,12 +354,10 @@ __global__ __launch_bounds__(kDecThreads, GC == 1 ? 4 : 2) void decode_kernel(Pl
       if (t0 + BATCH <= min(c1, key1)) {         // consecutive tokens of one range (nearly every batch)
         const int64_t stride = uniform64(tab.stride[i0]), off = (t0 - c0 + kgw) * stride + sub * 16;
         const char *kp = tab.k[i0] + off, *vp = tab.v[i0] + off;
-        // non-temporal: a row is read once, or once per chunk of query heads (64 prompts of 32 heads, 430 keys: 103.1 ->
-        // 93.0 us, 5.8 TB/s)
 #pragma unroll
         for (int u = 0; u < kDecUnroll; ++u) {
-          bt.kraw[u] = ld16_stream(kp + u * KPI * stride);
-          bt.vraw[u] = ld16_stream(vp + u * KPI * stride);
+          bt.kraw[u] = ld16_kv<STREAM>(kp + u * KPI * stride);
+          bt.vraw[u] = ld16_kv<STREAM>(vp + u * KPI * stride);
           bt.pk[u] = BIAS ? tab.pos[i0][t0 - c0 + kgw + u * KPI] : 0.f;
         }
       } else {
@@ -363,9 +367,9 @@ __global__ __launch_bounds__(kDecThreads, GC == 1 ? 4 : 2) void decode_kernel(Pl
           const int mine = t0 + kgw + u * KPI, vk = min(mine, key1 - 1);
           const int i = find.from(i0, vk);
           const int64_t off = int64_t(vk - tab.cum[i]) * tab.stride[i] + sub * 16;
-          bt.kraw[u] = ld16_stream(tab.k[i] + off);
+          bt.kraw[u] = ld16_kv<STREAM>(tab.k[i] + off);
           bt.vraw[u] = u32x4{0, 0, 0, 0};
-          if (mine < key1) bt.vraw[u] = ld16_stream(tab.v[i] + off);
+          if (mine < key1) bt.vraw[u] = ld16_kv<STREAM>(tab.v[i] + off);
           bt.pk[u] = BIAS ? tab.pos[i][vk - tab.cum[i]] : 0.f;
         }
       }
@@ -479,7 +483,7 @@ __device__ __forceinline__ void static_for(F &&f) {
 //                  16 bytes each, and take p of head h from lane h of their row (a row broadcast, no LDS).
 // The vector-unit form spends a dot product and a reduction over 16 lanes per key and head; here a tile of 16 keys takes
 // about 40 % of its vector instructions at four heads (64 prompts of 32/8 heads, 430 keys: 33.9 -> 25.9 us).
-template <int D, int GC, bool BIAS>
+template <int D, int GC, bool BIAS, bool STREAM>
 __global__ __launch_bounds__(kDecThreads) void decode_gqa_kernel(PlanDev pd, DecodeDev a) {
   constexpr int NJ = D / 32;                 // matrix products per tile
   constexpr int LPR = D / 8;                 // lanes per V row: 16, or 8 (then a row of 16 lanes reads two keys at once)
@@ -524,8 +528,8 @@ __global__ __launch_bounds__(kDecThreads) void decode_gqa_kernel(PlanDev pd, Dec
       const int c0 = __builtin_amdgcn_readfirstlane(tab.cum[i0]), c1 = __builtin_amdgcn_readfirstlane(tab.cum[i0 + 1]);
       if (t0 + 16 * U <= min(c1, key1)) {
         // All keys of the step are consecutive tokens of one range (nearly every step).  V rows, whole in one load, are
-        // read non-temporally; K rows are not, since four loads share a row's lines (64 prompts of 32/8 heads, 590 keys:
-        // V 39.6 -> 37.5 us, both 38.4).
+        // read non-temporally where no other workgroup reads them; K rows are not, since four loads share a row's lines
+        // (64 prompts of 32/8 heads, 590 keys: V 39.6 -> 37.5 us, both 38.4).
         const int64_t stride = uniform64(tab.stride[i0]);
         const char *kp = tab.k[i0] + (t0 - c0 + r) * stride + g * 16;
         const char *vp = tab.v[i0] + (t0 - c0 + 4 * g + vhalf) * stride + vc * 16;
@@ -535,7 +539,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_gqa_kernel(PlanDev pd, Dec
           for (int j = 0; j < NJ; ++j)
             kf[u][j] = *reinterpret_cast<const bf16x8 *>(kp + 16 * u * stride + 64 * j);
 #pragma unroll
-          for (int i = 0; i < NV; ++i) vf[u][i] = ld16_stream(vp + (16 * u + i * (LPR == 8 ? 2 : 1)) * stride);
+          for (int i = 0; i < NV; ++i) vf[u][i] = ld16_kv<STREAM>(vp + (16 * u + i * (LPR == 8 ? 2 : 1)) * stride);
           if (BIAS)
 #pragma unroll
             for (int i = 0; i < 4; ++i) pk[u][i] = tab.pos[i0][t0 - c0 + 16 * u + 4 * g + i];
@@ -553,7 +557,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_gqa_kernel(PlanDev pd, Dec
             vf[u][i] = u32x4{0, 0, 0, 0};                          // no key, no V: its weight is zero, and 0 * inf is not
             if (vk < key1) {
               const int iv = find.from(i0, vk);
-              vf[u][i] = ld16_stream(tab.v[iv] + int64_t(vk - tab.cum[iv]) * tab.stride[iv] + vc * 16);
+              vf[u][i] = ld16_kv<STREAM>(tab.v[iv] + int64_t(vk - tab.cum[iv]) * tab.stride[iv] + vc * 16);
             }
           }
           if (BIAS)
@@ -685,11 +689,17 @@ static hipError_t launch_decode_t(const sp_plan *plan, DecodeDev &d, const Decod
     }
   }
   const dim3 grid(unsigned(base), unsigned(ny), unsigned(d.n_pieces / d.pieces_per_wg)), block(kDecThreads);
-  auto launch = [&](auto heads, auto bias) {
+  auto launch_as = [&](auto heads, auto bias, auto stream) {
     constexpr int GC = decltype(heads)::value;
-    constexpr bool BIAS = decltype(bias)::value;
-    if constexpr (kBf16 && GC > 1) hipLaunchKernelGGL((decode_gqa_kernel<D, GC, BIAS>), grid, block, 0, s, plan->dev, d);
-    else if constexpr (GC <= 4) hipLaunchKernelGGL((decode_kernel<T, D, GC, BIAS>), grid, block, 0, s, plan->dev, d);
+    constexpr bool BIAS = decltype(bias)::value, STREAM = decltype(stream)::value;
+    if constexpr (kBf16 && GC > 1) hipLaunchKernelGGL((decode_gqa_kernel<D, GC, BIAS, STREAM>), grid, block, 0, s, plan->dev, d);
+    else if constexpr (GC <= 4) hipLaunchKernelGGL((decode_kernel<T, D, GC, BIAS, STREAM>), grid, block, 0, s, plan->dev, d);
+  };
+  auto launch = [&](auto heads, auto bias) {
+    // bf16 has several chunks only of eight heads
+    if constexpr (!kBf16 || decltype(heads)::value == 8)
+      if (ny > 1) return launch_as(heads, bias, std::false_type{});
+    launch_as(heads, bias, std::true_type{});
   };
   auto pick = [&](auto bias) {
     if (gc == 8) launch(std::integral_constant<int, 8>{}, bias);
