@@ -127,8 +127,12 @@ __device__ __forceinline__ void build_key_table(const PlanDev &pd, const DecodeD
   __syncthreads();
 }
 
+// K, V and positions are read through pointers from the table: see global_ptr
 template <bool STREAM>
-__device__ __forceinline__ u32x4 ld16_kv(const void *p) { return STREAM ? ld16_stream(p) : ld16(p); }
+__device__ __forceinline__ u32x4 ld16_kv(const char *p) {
+  if constexpr (STREAM) return __builtin_nontemporal_load(global_ptr<u32x4>(p));
+  else return *global_ptr<u32x4>(p);
+}
 
 // Range of a key (vk < n_total, so every search ends at the latest on the new token's range).  Every lane keeps one
 // running count, so that the range of a wave-uniform key is one comparison and a bit count; walking the counts in LDS
@@ -358,23 +362,26 @@ __global__ __launch_bounds__(kDecThreads, GC == 1 ? 4 : 2) void decode_kernel(Pl
         for (int u = 0; u < kDecUnroll; ++u) {
           bt.kraw[u] = ld16_kv<STREAM>(kp + u * KPI * stride);
           bt.vraw[u] = ld16_kv<STREAM>(vp + u * KPI * stride);
-          bt.pk[u] = BIAS ? tab.pos[i0][t0 - c0 + kgw + u * KPI] : 0.f;
+          bt.pk[u] = BIAS ? global_ptr<float>(tab.pos[i0])[t0 - c0 + kgw + u * KPI] : 0.f;
         }
       } else {
 #pragma unroll
         for (int u = 0; u < kDecUnroll; ++u) {
-          // lanes past the end re-read the last key's K and take zeros for V, whose weight is zero: 0 * inf is not 0
-          const int mine = t0 + kgw + u * KPI, vk = min(mine, key1 - 1);
+          const int vk = min(t0 + kgw + u * KPI, key1 - 1);      // lanes past the end re-read the last key
           const int i = find.from(i0, vk);
           const int64_t off = int64_t(vk - tab.cum[i]) * tab.stride[i] + sub * 16;
           bt.kraw[u] = ld16_kv<STREAM>(tab.k[i] + off);
-          bt.vraw[u] = u32x4{0, 0, 0, 0};
-          if (mine < key1) bt.vraw[u] = ld16_kv<STREAM>(tab.v[i] + off);
-          bt.pk[u] = BIAS ? tab.pos[i][vk - tab.cum[i]] : 0.f;
+          bt.vraw[u] = ld16_kv<STREAM>(tab.v[i] + off);
+          bt.pk[u] = BIAS ? global_ptr<float>(tab.pos[i])[vk - tab.cum[i]] : 0.f;
         }
       }
     };
-    auto compute_batch = [&](int t0, const Batch &bt) {
+    auto compute_batch = [&](int t0, Batch &bt) {
+      if (t0 + BATCH > key1) {                   // lanes past the end: their weight is zero, but 0 * inf is not
+#pragma unroll
+        for (int u = 0; u < kDecUnroll; ++u)
+          if (t0 + kgw + u * KPI >= key1) bt.vraw[u] = u32x4{0, 0, 0, 0};
+      }
       float t[kDecUnroll][GC];
 #pragma unroll
       for (int u = 0; u < kDecUnroll; ++u) {
@@ -537,12 +544,12 @@ __global__ __launch_bounds__(kDecThreads) void decode_gqa_kernel(PlanDev pd, Dec
         for (int u = 0; u < U; ++u) {
 #pragma unroll
           for (int j = 0; j < NJ; ++j)
-            kf[u][j] = *reinterpret_cast<const bf16x8 *>(kp + 16 * u * stride + 64 * j);
+            kf[u][j] = *global_ptr<bf16x8>(kp + 16 * u * stride + 64 * j);
 #pragma unroll
           for (int i = 0; i < NV; ++i) vf[u][i] = ld16_kv<STREAM>(vp + (16 * u + i * (LPR == 8 ? 2 : 1)) * stride);
           if (BIAS)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) pk[u][i] = tab.pos[i0][t0 - c0 + 16 * u + 4 * g + i];
+            for (int i = 0; i < 4; ++i) pk[u][i] = global_ptr<float>(tab.pos[i0])[t0 - c0 + 16 * u + 4 * g + i];
         }
       } else {
 #pragma unroll
@@ -550,21 +557,17 @@ __global__ __launch_bounds__(kDecThreads) void decode_gqa_kernel(PlanDev pd, Dec
           const int kk = min(t0 + 16 * u + r, key1 - 1), ik = find.from(i0, kk);
           const char *kp = tab.k[ik] + int64_t(kk - tab.cum[ik]) * tab.stride[ik] + g * 16;
 #pragma unroll
-          for (int j = 0; j < NJ; ++j) kf[u][j] = *reinterpret_cast<const bf16x8 *>(kp + 64 * j);
+          for (int j = 0; j < NJ; ++j) kf[u][j] = *global_ptr<bf16x8>(kp + 64 * j);
 #pragma unroll
           for (int i = 0; i < NV; ++i) {
-            const int vk = t0 + 16 * u + 4 * g + (LPR == 8 ? 2 * i + vhalf : i);
-            vf[u][i] = u32x4{0, 0, 0, 0};                          // no key, no V: its weight is zero, and 0 * inf is not
-            if (vk < key1) {
-              const int iv = find.from(i0, vk);
-              vf[u][i] = ld16_kv<STREAM>(tab.v[iv] + int64_t(vk - tab.cum[iv]) * tab.stride[iv] + vc * 16);
-            }
+            const int vk = min(t0 + 16 * u + 4 * g + (LPR == 8 ? 2 * i + vhalf : i), key1 - 1), iv = find.from(i0, vk);
+            vf[u][i] = ld16_kv<STREAM>(tab.v[iv] + int64_t(vk - tab.cum[iv]) * tab.stride[iv] + vc * 16);
           }
           if (BIAS)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               const int vk = min(t0 + 16 * u + 4 * g + i, key1 - 1), iv = find.from(i0, vk);
-              pk[u][i] = tab.pos[iv][vk - tab.cum[iv]];
+              pk[u][i] = global_ptr<float>(tab.pos[iv])[vk - tab.cum[iv]];
             }
         }
       }
@@ -602,7 +605,9 @@ __global__ __launch_bounds__(kDecThreads) void decode_gqa_kernel(PlanDev pd, Dec
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
           float v[8];
-          Elem<__bf16>::unpack(vf[u][i], v);
+          // no V without a key: its weight is zero, but 0 * inf is not (a branch around a step's masking costs 2 %)
+          const uint32_t keep = t0 + 16 * u + 4 * g + (LPR == 8 ? 2 * i + vhalf : i) < key1 ? ~0u : 0u;
+          Elem<__bf16>::unpack(vf[u][i] & u32x4{keep, keep, keep, keep}, v);
           static_for<0, GC>([&](auto hc) {
             constexpr int h = decltype(hc)::value;
             float p;

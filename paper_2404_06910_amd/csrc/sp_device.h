@@ -40,6 +40,13 @@ template <> struct Elem<__bf16> {
   __device__ static __forceinline__ void store1(__bf16 *p, float v) { *p = static_cast<__bf16>(v); }
 };
 
+// A pointer whose origin the compiler cannot see (read from a table) as one into global memory: loads through it count in
+// vmcnt alone, while a flat load is also waited for as an LDS access, with everything that is in flight.
+template <typename T>
+__device__ __forceinline__ const __attribute__((address_space(1))) T *global_ptr(const void *p) {
+  return (const __attribute__((address_space(1))) T *)p;
+}
+
 __device__ __forceinline__ u32x4 ld16(const void *p) { return *reinterpret_cast<const u32x4 *>(p); }
 __device__ __forceinline__ u32x4 ld16_stream(const void *p) {      // read-once data: do not keep in cache
   return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
