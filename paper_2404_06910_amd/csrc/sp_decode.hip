@@ -304,8 +304,10 @@ __device__ __forceinline__ void run_pieces(const PlanDev &pd, const DecodeDev &a
 // STREAM: a workgroup reads its K and V rows alone (one chunk of query heads per KV head), so they are read non-temporally
 // (64 prompts of 32 heads, 430 keys: 103.1 -> 93.0 us, 5.8 TB/s).  Where several chunks read the same rows, cached loads let
 // the later ones find them in the caches (64 fp32 prompts of 40/4 heads, five chunks: non-temporally 100.7, cached 77.7 us).
+// Four waves per SIMD for one head, except that bf16 with positions does not fit their 128 registers: with three it takes
+// 135 and spills none (64 prompts, 32 heads: 101.1 -> 87.5 us; at four, 6 spilled).
 template <typename T, int D, int GC, bool BIAS, bool STREAM>
-__global__ __launch_bounds__(kDecThreads, GC == 1 ? 4 : 2) void decode_kernel(PlanDev pd, DecodeDev a) {
+__global__ __launch_bounds__(kDecThreads, GC == 1 ? (BIAS && sizeof(T) == 2 ? 3 : 4) : 2) void decode_kernel(PlanDev pd, DecodeDev a) {
   constexpr int EV = Elem<T>::kVec;       // elements per 16-byte lane load
   constexpr int LPK = D / EV;             // lanes per key row
   constexpr int KPI = 64 / LPK;           // key rows per load instruction of a wave

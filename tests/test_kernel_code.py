@@ -47,3 +47,8 @@ def test_decode_loads_are_global(kernels):
         assert not [c for c in code if c.startswith("flat_load")], name
         # K and V of the next batch (or V of this one) stay in flight across the first products
         assert any(re.match(r"s_waitcnt vmcnt\([1-9]", c) for c in code), name
+
+
+def test_decode_keeps_its_registers(kernels):
+    for name, code in _named(kernels, "decode").items():
+        assert not [c for c in code if c.startswith("scratch_")], name
