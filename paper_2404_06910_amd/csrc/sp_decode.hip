@@ -52,6 +52,7 @@ struct DecodeDev {
   int32_t pieces_per_wg;   // n_pieces (one workgroup does them all, in order) or 1
   float *part;             // with one workgroup per piece: [row][piece][D] sums, then [row][piece] {max, sum}
   uint32_t *count;         // and one arrival counter per (prompt, KV head, chunk of query heads), zero between launches
+  int32_t chunks_together; // see my_share
 };
 
 // The key list of one (prompt, KV head) as ranges with running key counts, in LDS: the prefill ranges of the
@@ -160,6 +161,18 @@ __device__ __forceinline__ int64_t uniform64(int64_t x) {
   return int64_t((uint64_t(hi) << 32) | lo);
 }
 
+// What a workgroup does: (prompt, KV head) pair and chunk of that head's query heads.  With several chunks (!STREAM) and
+// pairs that divide by 8, the chunks of a pair follow each other on one XCD (workgroups go round the 8 XCDs) and find the
+// pair's K and V in its L2.  64 fp32 prompts, us with all pairs' first chunk before any second / as here: 28/4 heads (seven
+// chunks) 114.5 / 58.9, 36/4 (nine) 150.5 / 70.9, 40/4 (five) 73.8 / 71.7.
+struct Share { int pair, chunk; };
+template <bool STREAM>
+__device__ __forceinline__ Share my_share(const DecodeDev &a) {
+  if (STREAM) return {int(blockIdx.x), 0};
+  if (a.chunks_together) return {int(blockIdx.z * 8 + blockIdx.x % 8), int(blockIdx.x / 8)};
+  return {int(blockIdx.x), int(blockIdx.z)};
+}
+
 // rows of the response cache that take part (the new token is not one of them), and the row the new token goes to
 struct RespRows { int read, write; };
 __device__ __forceinline__ RespRows resp_rows(const DecodeDev &a, int b) {
@@ -226,11 +239,11 @@ struct PieceMerge {
 // zero.  There is no device-scope fence on purpose: it would write back and invalidate the whole L2 (measured: 67 us
 // for a step), while the stores and loads here bypass it for these few kilobytes alone.
 template <typename T, int D, int GC, int NG, class ComputePiece>
-__device__ __forceinline__ void run_pieces(const PlanDev &pd, const DecodeDev &a, int b, int head0, int n_heads,
+__device__ __forceinline__ void run_pieces(const PlanDev &pd, const DecodeDev &a, Share me, int b, int head0, int n_heads,
                                            int n_total, GroupSums<D, GC, NG> &s, ComputePiece &&compute) {
   using PM = PieceMerge<D, GC>;
   const int tid = threadIdx.x, Hq = pd.n_q_heads;
-  const int first = a.pieces_per_wg == 1 ? int(blockIdx.z) : 0;
+  const int first = a.pieces_per_wg == 1 ? int(blockIdx.y) : 0;
   // pieces are multiples of 16 keys
   const int chunk = ((n_total + a.n_pieces - 1) / a.n_pieces + 15) & ~15;
   PM run;
@@ -265,7 +278,7 @@ __device__ __forceinline__ void run_pieces(const PlanDev &pd, const DecodeDev &a
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wave's stores have been performed
     __syncthreads();
     if (tid == 0) {
-      uint32_t *ctr = a.count + (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+      uint32_t *ctr = a.count + (me.chunk * pd.n_prompts * pd.n_kv_heads + me.pair);
       const uint32_t before = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       s_last = before == uint32_t(a.n_pieces - 1);
       if (s_last) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -314,8 +327,9 @@ __global__ __launch_bounds__(kDecThreads, GC == 1 ? (BIAS && sizeof(T) == 2 ? 3 
   constexpr int KPW = KPI * kDecWaves;    // key groups of the workgroup
   constexpr int BATCH = KPI * kDecUnroll;
   const int Hq = pd.n_q_heads, Hkv = pd.n_kv_heads, G = Hq / Hkv;
-  const int b = blockIdx.x / Hkv, g = blockIdx.x % Hkv;
-  const int head0 = g * G + blockIdx.y * GC;
+  const Share me = my_share<STREAM>(a);
+  const int b = me.pair / Hkv, g = me.pair % Hkv;
+  const int head0 = g * G + me.chunk * GC;
   const int tid = threadIdx.x, kg = tid / LPK, sub = tid % LPK;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), kgw = (tid & 63) / LPK;
 
@@ -336,11 +350,11 @@ __global__ __launch_bounds__(kDecThreads, GC == 1 ? (BIAS && sizeof(T) == 2 ? 3 
     slope2[c] = BIAS ? pd.slopes[head0 + c] * kLog2e : 0.f;
   }
   const RespRows rr = resp_rows(a, b);
-  if (blockIdx.y == 0 && blockIdx.z == 0) append_new<T, D>(pd, a, b, g, rr.write);
+  if (me.chunk == 0 && blockIdx.y == 0) append_new<T, D>(pd, a, b, g, rr.write);
   build_key_table<T, D>(pd, a, b, g, rr.read, BIAS, tab);
   const RangeSearch find(tab);
 
-  run_pieces<T, D, GC, KPW>(pd, a, b, head0, GC, tab.n_total, sums, [&](int key0, int key1) {
+  run_pieces<T, D, GC, KPW>(pd, a, me, b, head0, GC, tab.n_total, sums, [&](int key0, int key1) {
     float m[GC], l[GC], acc[GC][EV];
 #pragma unroll
     for (int c = 0; c < GC; ++c) {
@@ -499,8 +513,9 @@ __global__ __launch_bounds__(kDecThreads) void decode_gqa_kernel(PlanDev pd, Dec
   constexpr int NV = LPR / 4;                // V loads per tile
   constexpr int U = 2;                       // tiles in flight per wave
   const int Hq = pd.n_q_heads, Hkv = pd.n_kv_heads, G = Hq / Hkv;
-  const int b = blockIdx.x / Hkv, kvh = blockIdx.x % Hkv;
-  const int head0 = kvh * G + blockIdx.y * GC, n_heads = min(GC, G - int(blockIdx.y) * GC);
+  const Share me = my_share<STREAM>(a);
+  const int b = me.pair / Hkv, kvh = me.pair % Hkv;
+  const int head0 = kvh * G + me.chunk * GC, n_heads = min(GC, G - me.chunk * GC);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, r = lane & 15, vc = lane % LPR, vhalf = LPR == 8 ? (lane >> 3) & 1 : 0;
 
@@ -517,11 +532,11 @@ __global__ __launch_bounds__(kDecThreads) void decode_gqa_kernel(PlanDev pd, Dec
   const float slope2 = BIAS ? pd.slopes[my_head] * kLog2e : 0.f;
   const float pos_q = BIAS ? a.new_pos[b] : 0.f;
   const RespRows rr = resp_rows(a, b);
-  if (blockIdx.y == 0 && blockIdx.z == 0) append_new<__bf16, D>(pd, a, b, kvh, rr.write);
+  if (me.chunk == 0 && blockIdx.y == 0) append_new<__bf16, D>(pd, a, b, kvh, rr.write);
   build_key_table<__bf16, D>(pd, a, b, kvh, rr.read, BIAS, tab);
   const RangeSearch find(tab);
 
-  run_pieces<__bf16, D, GC, kDecWaves>(pd, a, b, head0, n_heads, tab.n_total, sums, [&](int key0, int key1) {
+  run_pieces<__bf16, D, GC, kDecWaves>(pd, a, me, b, head0, n_heads, tab.n_total, sums, [&](int key0, int key1) {
     float m = kNegBig, l = 0.f;              // of (keys of row g, head r)
     float acc[GC][8];
 #pragma unroll
@@ -695,7 +710,10 @@ static hipError_t launch_decode_t(const sp_plan *plan, DecodeDev &d, const Decod
       d.pieces_per_wg = 1;
     }
   }
-  const dim3 grid(unsigned(base), unsigned(ny), unsigned(d.n_pieces / d.pieces_per_wg)), block(kDecThreads);
+  d.chunks_together = ny > 1 && base % 8 == 0 && base / 8 <= 65535;
+  const unsigned n_z = unsigned(d.n_pieces / d.pieces_per_wg);
+  const dim3 grid = d.chunks_together ? dim3(8u * unsigned(ny), n_z, unsigned(base) / 8) : dim3(unsigned(base), n_z, unsigned(ny));
+  const dim3 block(kDecThreads);
   auto launch_as = [&](auto heads, auto bias, auto stream) {
     constexpr int GC = decltype(heads)::value;
     constexpr bool BIAS = decltype(bias)::value, STREAM = decltype(stream)::value;
@@ -720,7 +738,7 @@ static hipError_t launch_decode_t(const sp_plan *plan, DecodeDev &d, const Decod
 
 hipError_t launch_decode(const sp_plan *plan, const DecodeArgs &a, hipStream_t s) {
   DecodeDev d{a.kept, a.k, a.Kp, a.Vp, a.kv_tok_stride, a.kv_head_stride, a.Kr, a.Vr, a.pos_resp, a.resp_capacity,
-              a.resp_len, a.resp_len_add, a.new_pos, a.q_new, a.k_new, a.v_new, a.o_out, a.scale, 1, 1, nullptr, nullptr};
+              a.resp_len, a.resp_len_add, a.new_pos, a.q_new, a.k_new, a.v_new, a.o_out, a.scale, 1, 1, nullptr, nullptr, 0};
   if (plan->dtype == SP_BF16)
     return plan->head_dim == 128 ? launch_decode_t<__bf16, 128>(plan, d, a, s) : launch_decode_t<__bf16, 64>(plan, d, a, s);
   return plan->head_dim == 128 ? launch_decode_t<float, 128>(plan, d, a, s) : launch_decode_t<float, 64>(plan, d, a, s);
