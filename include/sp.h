@@ -24,9 +24,13 @@
  *   needs more allocates a larger block once and keeps the old one until sp_destroy, so a captured graph
  *   never names freed memory), so they may be captured into a HIP graph on the context's stream.
  *   A plan keeps its context alive: sp_destroy may be called before sp_plan_destroy.
- *   Decode launches that cut their key lists into pieces use scratch memory that sp_create allocates: 16 regions,
- *   one per stream (and per stream of a captured graph) the context has launched such a decode on; a launch that
- *   finds all of them taken runs without and gives the same bits, slower.
+ *   Decode launches that cut their key lists into pieces use scratch memory of the plan, one region per stream, and per
+ *   stream of each graph capture, that has launched a decode of the plan since it was made or updated.  The first
+ *   regions come with the plan's tables, further ones are allocated when they are first needed (also under capture; up
+ *   to 256).  A launch that gets none (the 257th, or on hipStreamPerThread) gives the same bits, slower: one workgroup
+ *   then does the pieces in turn.  The regions are given back with the plan's tables.  Hence: replays of one captured
+ *   decode must not overlap each other; after sp_plan_update, a graph captured before must not run beside other decodes
+ *   of the plan; and a stream must have finished its decodes before it is destroyed.
  */
 #ifndef SP_H_
 #define SP_H_

@@ -120,8 +120,9 @@ extern "C" const char *sp_version(void) { return "sp-forkjoin 0.1 (gfx950)"; }
 
 extern "C" const char *sp_last_error(const sp_ctx *ctx) { return ctx ? ctx->err.c_str() : g_err.c_str(); }
 
-static void *alloc_zeroed(size_t bytes) {
+static void *alloc_sal(int32_t slots, int64_t rows) {
   void *p = nullptr;
+  const size_t bytes = sp::saliency_scratch_bytes(rows, slots);
   if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
   // zero before any stream may use it: the memset runs on the null stream, the kernels on the caller's
   if (hipMemset(p, 0, bytes) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) {
@@ -130,8 +131,6 @@ static void *alloc_zeroed(size_t bytes) {
   }
   return p;
 }
-
-static void *alloc_sal(int32_t slots, int64_t rows) { return alloc_zeroed(sp::saliency_scratch_bytes(rows, slots)); }
 
 extern "C" sp_status sp_create(sp_ctx **out, int device, void *hip_stream) {
   if (!out) return fail(nullptr, SP_ERR_INVALID_ARG, "out is NULL");
@@ -153,10 +152,8 @@ extern "C" sp_status sp_create(sp_ctx **out, int device, void *hip_stream) {
   c->sal_slots = sp::kSalDefaultSlots;
   c->sal_rows = sp::kSalDefaultRows;
   c->sal = alloc_sal(c->sal_slots, c->sal_rows);
-  c->dec = alloc_zeroed(sp::kDecRegionBytes * sp::kDecRegions);
-  if (!c->sal || !c->dec || hipEventCreateWithFlags(&c->stage_ev, hipEventDisableTiming) != hipSuccess) {
+  if (!c->sal || hipEventCreateWithFlags(&c->stage_ev, hipEventDisableTiming) != hipSuccess) {
     if (c->sal) (void)hipFree(c->sal);
-    if (c->dec) (void)hipFree(c->dec);
     delete c;
     return fail(nullptr, SP_ERR_WORKSPACE, "could not allocate the context's workspace");
   }
@@ -165,9 +162,7 @@ extern "C" sp_status sp_create(sp_ctx **out, int device, void *hip_stream) {
 }
 
 static void ctx_unref(sp_ctx *ctx) {
-  if (--ctx->refs) return;
-  if (ctx->dec) (void)hipFree(ctx->dec);
-  delete ctx;
+  if (--ctx->refs == 0) delete ctx;
 }
 
 extern "C" void sp_destroy(sp_ctx *ctx) {
@@ -216,25 +211,61 @@ static sp_status ensure_sal(sp_ctx *ctx, int64_t n_rows, int32_t n_slots) {
   return SP_OK;
 }
 
+// Further decode regions for a plan, as many as it has.  This may happen while a stream is being captured: the allocation
+// and the zeroing (on a stream of its own, waited for) are no part of the capture, and the calls are made in the mode that
+// lets them be.
+static bool more_decode_regions(const sp_plan *p) {
+  const size_t have = p->dec_regions.size(), n = std::min(have, sp::kDecMaxRegions - have);
+  if (n == 0) return false;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
+  const size_t bytes = n * (p->dec_count_bytes + p->dec_part_bytes);
+  void *block = nullptr;
+  hipStream_t own = nullptr;
+  bool ok = hipMalloc(&block, bytes) == hipSuccess && hipStreamCreateWithFlags(&own, hipStreamNonBlocking) == hipSuccess &&
+            hipMemsetAsync(block, 0, n * p->dec_count_bytes, own) == hipSuccess && hipStreamSynchronize(own) == hipSuccess;
+  if (own) (void)hipStreamDestroy(own);
+  if (!ok && block) (void)hipFree(block);
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (!ok) return false;
+  p->dec_blocks.push_back({block, bytes});
+  for (size_t i = 0; i < n; ++i)
+    p->dec_regions.push_back({static_cast<char *>(block) + n * p->dec_count_bytes + i * p->dec_part_bytes,
+                              reinterpret_cast<uint32_t *>(static_cast<char *>(block) + i * p->dec_count_bytes), nullptr, 0, false});
+  return true;
+}
+
 // The region of the order of execution that a launch on `s` joins.  hipStreamPerThread names another stream in every
-// thread and gets none; neither does a launch for which all regions are taken.
-void *sp::decode_region(sp_ctx *ctx, hipStream_t s) {
-  if (s == hipStreamPerThread) return nullptr;
-  unsigned long long capture = 0;
+// thread and gets none.  Errors are dealt with here: the launch that follows reports its own.
+const sp::DecodeRegion *sp::decode_region(const sp_plan *p, hipStream_t s) {
+  if (s == hipStreamPerThread || p->dec_regions.empty()) return nullptr;
+  unsigned long long order = 0;
   if (s) {                                              // the null stream cannot be captured
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     unsigned long long id = 0;
-    if (hipStreamGetCaptureInfo(s, &st, &id) != hipSuccess) return nullptr;
-    if (st != hipStreamCaptureStatusNone) capture = id + 1;
+    if (hipStreamGetCaptureInfo(s, &st, &id) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    if (st != hipStreamCaptureStatusNone) order = id + 1;
   }
-  size_t i = 0;
-  for (; i < ctx->dec_owner.size(); ++i)
-    if (ctx->dec_owner[i].stream == s && ctx->dec_owner[i].capture == capture) break;
-  if (i == ctx->dec_owner.size()) {
-    if (i == size_t(sp::kDecRegions)) return nullptr;
-    ctx->dec_owner.push_back({s, capture});
+  DecodeRegion *unused = nullptr;
+  for (DecodeRegion &r : p->dec_regions) {
+    if (r.taken && r.stream == s && r.order == order) return &r;
+    if (!r.taken && !unused) unused = &r;
   }
-  return static_cast<char *>(ctx->dec) + i * sp::kDecRegionBytes;
+  if (!unused) {
+    const size_t have = p->dec_regions.size();
+    if (!more_decode_regions(p)) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    unused = &p->dec_regions[have];
+  }
+  unused->stream = s;
+  unused->order = order;
+  unused->taken = true;
+  return unused;
 }
 
 namespace {
@@ -537,6 +568,7 @@ sp_status build_plan(sp_ctx *ctx, const sp_segtable *t, int32_t n_q_heads, int32
       p->max_path_keys = std::max(p->max_path_keys, path_keys);
     }
   }
+  sp::decode_scratch(p, n_cu, &p->dec_part_bytes, &p->dec_count_bytes);
   return SP_OK;
 }
 
@@ -571,7 +603,10 @@ sp_status upload_plan(sp_ctx *ctx, sp_plan *p, void *reuse_blob, size_t reuse_by
                o_sd = add(shared_desc.data(), shared_desc.size() * sizeof(sp::RangeDesc)),
                o_pd = add(path_desc.data(), path_desc.size() * sizeof(sp::RangeDesc)),
                o_dr = add(p->dec_ranges.data(), p->dec_ranges.size() * sizeof(sp::KeyRange));
-  const size_t total = off + 256;
+  // decode regions: their counters travel with the tables (as zeros), the partial sums lie behind all that travels
+  const size_t n_regions = p->dec_part_bytes ? size_t(ctx->dec_regions) : 0;
+  const size_t o_count = (off + 255) & ~size_t(255), o_part = o_count + n_regions * p->dec_count_bytes + 256;
+  const size_t upload = o_part, total = o_part + n_regions * p->dec_part_bytes;
   SP_HIP(ctx, hipSetDevice(ctx->device));
   // device block: the plan's own (an update), else the smallest pooled block that fits, else a new one
   void *blob = nullptr;
@@ -599,11 +634,11 @@ sp_status upload_plan(sp_ctx *ctx, sp_plan *p, void *reuse_blob, size_t reuse_by
     if (e != hipSuccess) { give_back(); return fail(&ctx->err, SP_ERR_HIP, "plan upload: %s", hipGetErrorString(e)); }
     ctx->stage_busy = false;
   }
-  if (ctx->stage_bytes < total) {
+  if (ctx->stage_bytes < upload) {
     if (ctx->stage) (void)hipHostFree(ctx->stage);
     ctx->stage = nullptr;
     ctx->stage_bytes = 0;
-    const size_t want = std::max(total + total / 4, size_t(1) << 20);
+    const size_t want = std::max(upload + upload / 4, size_t(1) << 20);
     if (hipHostMalloc(&ctx->stage, want, hipHostMallocDefault) != hipSuccess) {
       give_back();
       return fail(&ctx->err, SP_ERR_WORKSPACE, "could not allocate %zu bytes of pinned staging memory", want);
@@ -613,7 +648,8 @@ sp_status upload_plan(sp_ctx *ctx, sp_plan *p, void *reuse_blob, size_t reuse_by
   char *stg = static_cast<char *>(ctx->stage);
   for (auto &pc : pieces)
     if (pc.bytes) std::memcpy(stg + pc.at, pc.src, pc.bytes);
-  hipError_t e = hipMemcpyAsync(blob, stg, total, hipMemcpyHostToDevice, ctx->stream);
+  if (n_regions) std::memset(stg + o_count, 0, n_regions * p->dec_count_bytes);
+  hipError_t e = hipMemcpyAsync(blob, stg, upload, hipMemcpyHostToDevice, ctx->stream);
   if (e == hipSuccess) e = hipEventRecord(ctx->stage_ev, ctx->stream);
   if (e != hipSuccess) { give_back(); return fail(&ctx->err, SP_ERR_HIP, "plan upload: %s", hipGetErrorString(e)); }
   ctx->stage_busy = true;
@@ -637,7 +673,28 @@ sp_status upload_plan(sp_ctx *ctx, sp_plan *p, void *reuse_blob, size_t reuse_by
   d.n_tokens = p->n_tokens;
   d.n_prompts = p->n_prompts;
   d.n_q_heads = p->n_q_heads; d.n_kv_heads = p->n_kv_heads; d.head_dim = p->head_dim;
+  p->dec_regions.clear();
+  p->dec_in_blob = n_regions;
+  for (size_t i = 0; i < n_regions; ++i)
+    p->dec_regions.push_back({base + o_part + i * p->dec_part_bytes,
+                              reinterpret_cast<uint32_t *>(base + o_count + i * p->dec_count_bytes), nullptr, 0, false});
   return SP_OK;
+}
+
+// Device memory of a plan that goes: kept for the next plan (work that still uses it is ordered before the next upload on the
+// same stream); a closed context has nothing to keep it in.
+void give_back_block(sp_ctx *ctx, void *block, size_t bytes) {
+  if (ctx && !ctx->closed && ctx->blob_pool.size() < 8) ctx->blob_pool.push_back({block, bytes});
+  else (void)hipFree(block);
+}
+
+void drop_decode_blocks(sp_ctx *ctx, sp_plan *p) {
+  size_t used = 0;
+  for (const sp::DecodeRegion &r : p->dec_regions) used += r.taken;
+  if (ctx && used) ctx->dec_regions = int(std::min<size_t>(std::max<size_t>(used, sp::kDecFirstRegions), sp::kDecPlanRegions));
+  for (auto &b : p->dec_blocks) give_back_block(ctx, b.first, b.second);
+  p->dec_blocks.clear();
+  p->dec_regions.clear();
 }
 
 }  // namespace
@@ -673,6 +730,15 @@ extern "C" sp_status sp_plan_update(sp_plan *plan, const sp_segtable *t) {
     st = upload_plan(ctx, &fresh, plan->dev_blob, plan->dev_blob_bytes);
     if (st != SP_OK) { fresh.dev_blob = nullptr; return st; }
   }
+  if (fresh.dec_part_bytes == plan->dec_part_bytes && fresh.dec_count_bytes == plan->dec_count_bytes) {
+    for (size_t i = plan->dec_in_blob; i < plan->dec_regions.size(); ++i) {
+      fresh.dec_regions.push_back(plan->dec_regions[i]);
+      fresh.dec_regions.back().taken = false;
+    }
+    fresh.dec_blocks = std::move(plan->dec_blocks);
+  } else {
+    drop_decode_blocks(ctx, plan);
+  }
   *plan = std::move(fresh);
   fresh.dev_blob = nullptr;
   return SP_OK;
@@ -681,12 +747,8 @@ extern "C" sp_status sp_plan_update(sp_plan *plan, const sp_segtable *t) {
 extern "C" void sp_plan_destroy(sp_plan *plan) {
   if (!plan) return;
   sp_ctx *ctx = plan->ctx;
-  if (plan->dev_blob) {
-    // keep the block for the next plan of this context (work that still reads it is ordered before
-    // the next upload on the same stream); a closed context has nothing to keep it in
-    if (ctx && !ctx->closed && ctx->blob_pool.size() < 8) ctx->blob_pool.push_back({plan->dev_blob, plan->dev_blob_bytes});
-    else (void)hipFree(plan->dev_blob);
-  }
+  if (plan->dev_blob) give_back_block(ctx, plan->dev_blob, plan->dev_blob_bytes);
+  drop_decode_blocks(ctx, plan);
   delete plan;
   if (ctx) ctx_unref(ctx);
 }

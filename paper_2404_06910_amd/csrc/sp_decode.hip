@@ -691,22 +691,37 @@ static int decode_pieces(int base_wgs, int64_t rows, int64_t keys, int gc, bool 
   return int(std::max<int64_t>(n, 1));
 }
 
+// How the heads of a plan are shared out: query heads per workgroup, (prompt, KV head) pairs, chunks per pair.  bf16 pads a
+// group to 2, 4 or 8 columns of the matrix product (a KV head with more than 8 query heads takes several workgroups);
+// fp32 takes the largest divisor of the group up to 4.
+struct HeadShares { int gc, pairs, chunks; };
+static HeadShares head_shares(const sp_plan *plan) {
+  const int G = plan->n_q_heads / plan->n_kv_heads;
+  const int gc = plan->dtype == SP_BF16 ? (G == 1 ? 1 : G == 2 ? 2 : G <= 4 ? 4 : 8) : (G % 4 == 0) ? 4 : (G % 2 == 0) ? 2 : 1;
+  return {gc, plan->n_prompts * plan->n_kv_heads, (G + gc - 1) / gc};
+}
+
+void decode_scratch(const sp_plan *plan, int n_cu, size_t *part_bytes, size_t *count_bytes) {
+  const HeadShares h = head_shares(plan);
+  const int64_t rows = int64_t(plan->n_prompts) * plan->n_q_heads, wgs = int64_t(h.pairs) * h.chunks;
+  const int most = wgs > kDecPartCounters ? 1 : decode_pieces(int(wgs), rows, INT64_MAX, h.gc, plan->dtype == SP_BF16, n_cu);
+  *part_bytes = most > 1 ? (size_t(rows) * most * (plan->head_dim + 2) * 4 + 255) & ~size_t(255) : 0;
+  *count_bytes = most > 1 ? (size_t(wgs) * 4 + 255) & ~size_t(255) : 0;
+}
+
 template <typename T, int D>
 static hipError_t launch_decode_t(const sp_plan *plan, DecodeDev &d, const DecodeArgs &a, hipStream_t s) {
-  const int G = plan->n_q_heads / plan->n_kv_heads;
   constexpr bool kBf16 = sizeof(T) == 2;
-  // query heads per workgroup: bf16 pads a group to 2, 4 or 8 columns of the matrix product (a KV head with more than
-  // 8 query heads takes several workgroups); fp32 takes the largest divisor of the group up to 4
-  const int gc = kBf16 ? (G == 1 ? 1 : G == 2 ? 2 : G <= 4 ? 4 : 8) : (G % 4 == 0) ? 4 : (G % 2 == 0) ? 2 : 1;
-  const int base = plan->n_prompts * plan->n_kv_heads, ny = (G + gc - 1) / gc;
+  const HeadShares h = head_shares(plan);
+  const int gc = h.gc, base = h.pairs, ny = h.chunks;
   const int64_t resp = int64_t(a.resp_len_add) + (a.resp_len ? a.resp_capacity / 2 : 0);
   const int64_t keys = plan->max_shared_keys + int64_t(a.k) * plan->max_path_keys + std::min<int64_t>(resp, a.resp_capacity);
   d.n_pieces = decode_pieces(base * ny, int64_t(plan->n_prompts) * plan->n_q_heads, keys, gc, kBf16, plan->ctx->n_cu);
   d.pieces_per_wg = d.n_pieces;
   if (d.n_pieces > 1) {
-    if (void *region = decode_region(plan->ctx, s)) {
-      d.part = static_cast<float *>(region);
-      d.count = reinterpret_cast<uint32_t *>(static_cast<char *>(region) + kDecPartBytes);
+    if (const DecodeRegion *region = decode_region(plan, s)) {
+      d.part = static_cast<float *>(region->part);
+      d.count = region->count;
       d.pieces_per_wg = 1;
     }
   }

@@ -38,13 +38,20 @@ inline size_t saliency_scratch_bytes(int64_t rows, int32_t slots) {
 static_assert(kSalSplitRows <= kSalDefaultRows && kSalSplitRows <= kSalStaticRows, "pieces of a call fit its scratch");
 constexpr size_t kSalStaticBytes = 256 + size_t(kSalStaticRows) * sizeof(RowPart) + sizeof(SalSlot) * size_t(kSalStaticSlots);
 
-// Scratch of a decode launch whose key lists are cut into pieces: partial sums of at most kDecPartRows (query row,
-// piece) pairs of up to 128 dims plus {max, sum} each, then the arrival counters (zero between launches).
+// A decode launch whose key lists are cut into pieces needs scratch, a region: partial sums of at most kDecPartRows (query
+// row, piece) pairs plus {max, sum} each, and at most kDecPartCounters arrival counters (zero between launches).
 constexpr int64_t kDecPartRows = 4096;
 constexpr int kDecPartCounters = 1024;
-constexpr size_t kDecPartBytes = size_t(kDecPartRows) * (128 + 2) * 4;
-constexpr size_t kDecRegionBytes = kDecPartBytes + size_t(kDecPartCounters) * 4;
-constexpr int kDecRegions = 16;
+// Regions that a plan's device block holds from the start (or as many as the plan destroyed last had in use, up to
+// kDecPlanRegions), and the most that a plan may come to have.
+constexpr int kDecFirstRegions = 4, kDecPlanRegions = 32, kDecMaxRegions = 256;
+struct DecodeRegion {
+  void *part;
+  uint32_t *count;
+  hipStream_t stream;             // owner: a stream, or a stream within one capture (order = capture id + 1, else 0)
+  unsigned long long order;
+  bool taken;
+};
 
 // A run of segments fused on the query side: child segments that are packed directly behind
 // their parent continue the parent's causal sequence (Sec. 3.2: a chain is a classical prompt).
@@ -123,12 +130,7 @@ struct sp_ctx {
   hipEvent_t stage_ev = nullptr;
   bool stage_busy = false;
   std::vector<std::pair<void *, size_t>> blob_pool;
-  // Decode scratch: kDecRegions regions of one block, made in sp_create.  A region belongs to one order of execution --
-  // a stream, or a stream within one capture -- for as long as the context lives, so that launches that may overlap
-  // never share one.  The block is freed with the last plan (a captured decode may be replayed until then).
-  struct DecodeOwner { hipStream_t stream; unsigned long long capture; };
-  void *dec = nullptr;
-  std::vector<DecodeOwner> dec_owner;
+  int dec_regions = sp::kDecFirstRegions;   // decode regions that the next plan starts with
   int refs = 1;               // the context itself + every live plan made on it
   bool closed = false;        // sp_destroy was called; the struct lives on until the last plan is gone
 };
@@ -160,7 +162,15 @@ struct sp_plan {
   std::vector<sp::KeyRange> dec_ranges;
   std::vector<int32_t> path_max_ranges;  // per prompt: max ranges of any single path
   std::vector<float> pos, slopes;        // copies of tok_pos / alibi_slopes (empty when not given)
-  // device copies (one allocation)
+  // Decode scratch (sp::DecodeRegion).  A region belongs to one order of execution -- a stream, or a stream within one
+  // capture -- until the plan is updated or destroyed, so that launches that may overlap never share one.  The regions
+  // follow the tables in the plan's device block, further ones come in blocks of their own; all go the way of the tables:
+  // whoever gets the memory next has work ordered behind the plan's, as sp_plan_update and sp_plan_destroy require.
+  size_t dec_part_bytes = 0, dec_count_bytes = 0;     // of one region; 0: no decode of this plan is cut into pieces
+  size_t dec_in_blob = 0;                             // regions in the device block; the others are in dec_blocks
+  mutable std::vector<sp::DecodeRegion> dec_regions;
+  mutable std::vector<std::pair<void *, size_t>> dec_blocks;
+  // device copies and decode scratch (one allocation)
   void *dev_blob = nullptr;
   size_t dev_blob_bytes = 0;  // capacity of the allocation
   sp::PlanDev dev{};
@@ -201,8 +211,10 @@ struct DecodeArgs {
   void *o_out;
   float scale;
 };
-// Scratch region for a decode launch on stream s, or nullptr when all are taken (the launch then does without).
-void *decode_region(sp_ctx *ctx, hipStream_t s);
+// bytes of partial sums and of counters that the largest decode of the plan needs (0: none is ever cut into pieces)
+void decode_scratch(const sp_plan *plan, int n_cu, size_t *part_bytes, size_t *count_bytes);
+// Scratch region for a decode launch on stream s, or nullptr when there is none to be had (the launch then does without).
+const DecodeRegion *decode_region(const sp_plan *plan, hipStream_t s);
 hipError_t launch_decode(const sp_plan *plan, const DecodeArgs &a, hipStream_t s);
 
 }  // namespace sp

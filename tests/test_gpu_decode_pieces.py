@@ -1,6 +1,6 @@
 """sp_pruned_decode where the key lists are long enough to be cut into pieces, and the grouped-head kernel: against the
 oracle, at key counts on and around the piece and tile boundaries, with every head grouping the dispatch knows; and the
-scratch regions of the pieces: streams of one context do not share one, and a launch that gets none agrees bit for bit."""
+scratch regions of the pieces: streams do not share one, and a launch that gets none agrees bit for bit."""
 import math
 
 import numpy as np
@@ -116,16 +116,17 @@ def test_more_ranges_than_a_wave_has_lanes(ctx, Hq, Hkv):
     _check(got.float().cpu().numpy(), x, st, [9], "bf16")
 
 
-def test_streams_have_their_own_scratch_and_running_out_changes_nothing():
-    """One context, 20 streams (there are 16 regions): overlapping launches on all of them give what a lone launch
-    gives, bit for bit, on the streams without a region too."""
-    print("case: decode on 20 streams of one context", flush=True)
+def test_streams_have_their_own_scratch_and_going_without_changes_nothing():
+    """One plan, 20 streams: overlapping launches on all of them give what a lone launch gives, bit for bit, and so do
+    launches on the per-thread stream, which get no scratch."""
+    print("case: decode on 20 streams of one plan", flush=True)
     ctx = B.Context(0)
     rng = np.random.default_rng(4)
     st = sp_synth.forkjoin_segtable(96, [[160, 200, 180, 220]] * 2, 24)
     xs = [_setup(ctx, rng, "bf16", 8, 2, 128, st, 3, [20, 90], False) for _ in range(20)]
     want = []
     for x in xs:
+        x["plan"] = xs[0]["plan"]
         want.append(_decode(ctx, x, "bf16"))
         torch.cuda.synchronize()
     got = [torch.full_like(w, float("nan")) for w in want]
@@ -137,5 +138,12 @@ def test_streams_have_their_own_scratch_and_running_out_changes_nothing():
             _decode(ctx, x, "bf16", o)
     torch.cuda.synchronize()
     for w, o in zip(want, got):
+        assert torch.equal(w, o)
+    ctx.sp_set_stream(2)                                 # hipStreamPerThread
+    for x, w in zip(xs[:3], want):
+        o = torch.full_like(w, float("nan"))
+        torch.cuda.synchronize()
+        _decode(ctx, x, "bf16", o)
+        torch.cuda.synchronize()
         assert torch.equal(w, o)
     ctx.close()
