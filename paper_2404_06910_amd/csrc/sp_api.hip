@@ -971,10 +971,11 @@ extern "C" sp_status sp_pruned_decode(sp_ctx *ctx, const sp_plan *plan, const in
   if (!(softmax_scale > 0.f) || !std::isfinite(softmax_scale))
     return fail(&ctx->err, SP_ERR_INVALID_ARG, "softmax_scale must be positive and finite");
   // joined-cache range count bound: shared ranges + k * (largest per-path range count)
-  int32_t worst = 0;
+  int64_t worst = 0;
   for (int32_t b = 0; b < plan->n_prompts; ++b)
-    worst = std::max(worst, plan->shared_rng_end[b] - plan->shared_rng_beg[b] + k * plan->path_max_ranges[b]);
-  if (worst > 120) return fail(&ctx->err, SP_ERR_UNSUPPORTED, "joined cache has %d disjoint ranges (limit 120)", worst);
+    worst = std::max(worst, plan->shared_rng_end[b] - plan->shared_rng_beg[b] + int64_t(k) * plan->path_max_ranges[b]);
+  if (worst > 120)
+    return fail(&ctx->err, SP_ERR_UNSUPPORTED, "joined cache has %lld disjoint ranges (limit 120)", (long long)worst);
   sp::DecodeArgs a{kept, k, K_prefill, V_prefill, kv_tok_stride, kv_head_stride, K_resp, V_resp, pos_resp,
                    resp_capacity, resp_len, resp_len_add, new_pos, q_new, k_new, v_new, o_out, softmax_scale};
   SP_HIP(ctx, hipSetDevice(ctx->device));

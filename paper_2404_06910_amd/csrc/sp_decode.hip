@@ -72,7 +72,7 @@ template <typename T, int D>
 __device__ __forceinline__ void build_key_table(const PlanDev &pd, const DecodeDev &a, int b, int g, int len_r, bool bias,
                                                 KeyTable &t) {
   const int tid = threadIdx.x, Hkv = pd.n_kv_heads;
-  const int n_src = min(a.k + 1, kDecMaxRanges);
+  const int n_src = min(a.k, kDecMaxRanges - 1) + 1;      // k beyond that: prompts without paths, nothing to keep
   RangeDesc src{0, 0, 0, 0};
   if (tid == 0) {
     src = pd.shared_desc[b];
