@@ -1,8 +1,8 @@
 // a1 (fp32 storage): ForkJoin prefill attention over the prompt DAG (Sec. 3.2, 3.2.1; App. B.3), the precision path
 // (tolerance 1e-4), on the fp32 matrix instruction: inputs, products, sums and probabilities stay in 32 bits.
 //
-// A work item of the plan is up to 32*NW/HPW consecutive rows of one row group for HPW query heads that share a KV head.
-// It is done by 2*NW one-wave workgroups; a wave owns 16 of its rows of one head and walks the rows' keys (ancestor ranges
+// A work item of the plan is up to tile_rows (16, 32 or 64) consecutive rows of one row group for HPW query heads that share
+// a KV head.  It is done by one-wave workgroups; a wave owns 16 of its rows of one head and walks the rows' keys (ancestor ranges
 // root to leaf, then the own run up to its last row) 16 at a time.  Per step, with v_mfma_f32_16x16x4_f32:
 //   S^T[key, row] = K[key, :] . Q[row, :]        A = K, B = Q (registers for the whole item)
 //   O^T[d, row]  += V^T[d, key] . P^T[key, row]  A = V, B = P as the first product leaves it
@@ -21,6 +21,8 @@
 // vector arithmetic, 161 us now.  In a profiled run, where it takes 176: 194 us with the waves of an item in one workgroup
 // (it keeps its place until its longest wave ends), 209 us with K and V staged through LDS for the four waves of an item.
 // Without the early K loads, at three waves per SIMD: 183 us where this one took 164.
+#include <algorithm>
+
 #include "sp_device.h"
 #include "sp_internal.h"
 
@@ -44,20 +46,21 @@ __device__ __forceinline__ float quad_sum(float x) {
 
 }  // namespace
 
-template <int D, int HPW, int NW, bool BIAS>
+template <int D, int HPW, bool BIAS>
 __global__ __launch_bounds__(64, 2) void prefill_f32_kernel(PlanDev pd, const float *__restrict__ Q,
                                                                   const float *__restrict__ K,
                                                                   const float *__restrict__ V, float *__restrict__ O,
                                                                   int64_t q_ts, int64_t q_hs, int64_t kv_ts,
-                                                                  int64_t kv_hs, float scale) {
+                                                                  int64_t kv_hs, float scale, int log2_waves,
+                                                                  int first_round) {
   constexpr int NI = D / 16;             // 16-byte vectors of a K or Q row per lane; 16-wide blocks of O^T
   constexpr int NH = D / 64;
-  // A block is one wave.  Blocks are dealt round-robin over the 8 XCDs and started in order: the 2 * NW waves of an item
-  // follow each other on one XCD, and an XCD works on a window of consecutive items of its own range of the list (slot
+  // A block is one wave.  Blocks are dealt round-robin over the 8 XCDs and started in order: the waves of an item follow
+  // each other on one XCD, and an XCD works on a window of consecutive items of its own range of the list (slot
   // x * (n_wg / 8) + i holds the items of XCD x that are i-th in its order, then the (i + n_wg / 8)-th, and so on).
-  const int xcd = blockIdx.x % 8, nth = blockIdx.x / 8, wave = nth % (2 * NW), per_xcd = pd.n_wg / 8;
-  const int slot = xcd * per_xcd + (nth / (2 * NW)) % per_xcd;
-  const int item = pd.wg_begin[slot] + nth / (2 * NW * per_xcd);
+  const int xcd = blockIdx.x % 8, nth = blockIdx.x / 8, wave = nth & ((1 << log2_waves) - 1), per_xcd = pd.n_wg / 8;
+  const int slot = xcd * per_xcd + (nth >> log2_waves) % per_xcd;
+  const int item = pd.wg_begin[slot] + first_round + (nth >> log2_waves) / per_xcd;
   if (item >= pd.wg_begin[slot + 1]) return;
   const WorkItem w = pd.items[item];
 
@@ -267,28 +270,34 @@ __global__ __launch_bounds__(64, 2) void prefill_f32_kernel(PlanDev pd, const fl
     }
 }
 
-template <int D, int HPW, int NW>
+template <int D, int HPW>
 static hipError_t launch_hpw(const sp_plan *plan, const PrefillArgs &a, hipStream_t s) {
-  const dim3 grid(unsigned(plan->n_wg) * unsigned(plan->max_slice) * 2 * NW);
-  if (grid.x == 0) return hipSuccess;                        // nothing is computed: every segment is cached
   const float *Q = static_cast<const float *>(a.Q), *K = static_cast<const float *>(a.K),
               *V = static_cast<const float *>(a.V);
   float *O = static_cast<float *>(a.O);
-  if (plan->has_slopes)
-    hipLaunchKernelGGL((prefill_f32_kernel<D, HPW, NW, true>), grid, dim3(64), 0, s, plan->dev, Q, K, V, O,
-                       a.q_tok_stride, a.q_head_stride, a.kv_tok_stride, a.kv_head_stride, a.scale);
-  else
-    hipLaunchKernelGGL((prefill_f32_kernel<D, HPW, NW, false>), grid, dim3(64), 0, s, plan->dev, Q, K, V, O,
-                       a.q_tok_stride, a.q_head_stride, a.kv_tok_stride, a.kv_head_stride, a.scale);
-  return hipGetLastError();
+  // one wave per 16 tile rows and head; rounds of one item per slot, in as many launches as 2^32 threads each allow
+  const int waves = plan->tile_rows / 16 * HPW, log2_waves = __builtin_ctz(unsigned(waves));
+  const int most = int((int64_t(1) << 32) / (int64_t(plan->n_wg) * waves * 64)) - 1;
+  for (int first = 0; first < plan->max_slice; first += most) {
+    const dim3 grid(unsigned(plan->n_wg) * unsigned(std::min(plan->max_slice - first, most)) * unsigned(waves));
+    if (plan->has_slopes)
+      hipLaunchKernelGGL((prefill_f32_kernel<D, HPW, true>), grid, dim3(64), 0, s, plan->dev, Q, K, V, O, a.q_tok_stride,
+                         a.q_head_stride, a.kv_tok_stride, a.kv_head_stride, a.scale, log2_waves, first);
+    else
+      hipLaunchKernelGGL((prefill_f32_kernel<D, HPW, false>), grid, dim3(64), 0, s, plan->dev, Q, K, V, O, a.q_tok_stride,
+                         a.q_head_stride, a.kv_tok_stride, a.kv_head_stride, a.scale, log2_waves, first);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;                                         // no round: every segment is cached
 }
 
 template <int D>
 static hipError_t launch_d(const sp_plan *plan, const PrefillArgs &a, hipStream_t s) {
   switch (plan->heads_per_wg) {
-    case 4: return launch_hpw<D, 4, 4>(plan, a, s);
-    case 2: return launch_hpw<D, 2, 2>(plan, a, s);
-    default: return launch_hpw<D, 1, 2>(plan, a, s);
+    case 4: return launch_hpw<D, 4>(plan, a, s);
+    case 2: return launch_hpw<D, 2>(plan, a, s);
+    default: return launch_hpw<D, 1>(plan, a, s);
   }
 }
 
