@@ -80,17 +80,20 @@ __global__ __launch_bounds__(64, 2) void prefill_f32_kernel(PlanDev pd, const fl
   // The key range that holds virtual key `base`: [base, base + len) are the tokens from tok on.  Range n_ranges is the
   // own run.  base, len and tok are the same for all lanes.
   int rng = -1, base = 0, len = 0, tok = 0;
+  // Range r, or the own run behind the last one (from virtual key b on).  The table is read in either case (a group without
+  // ranges reads the entry at its place in it, or the padding behind the table): a choice between two places to read from
+  // becomes a choice of addresses, with a flat load and a spilled register in every step that ends a range.
+  auto range = [&](int r, int b) -> KeyRange {
+    const KeyRange kr = pd.ranges[w.range_off + max(min(r, w.n_ranges - 1), 0)];
+    const bool own = r >= w.n_ranges;
+    return {own ? w.tok_start : kr.tok_start, own ? 0x7fffffff - b : kr.len};
+  };
   auto seek = [&](int vk) {
     while (vk >= base + len) {
       base += len;
-      if (++rng < w.n_ranges) {
-        const KeyRange kr = pd.ranges[w.range_off + rng];
-        tok = kr.tok_start;
-        len = kr.len;
-      } else {
-        tok = w.tok_start;
-        len = 0x7fffffff - base;
-      }
+      const KeyRange kr = range(++rng, base);
+      tok = kr.tok_start;
+      len = kr.len;
     }
   };
   // token of virtual key vk >= base; keys behind the last visible one (masked) repeat that one
@@ -99,14 +102,9 @@ __global__ __launch_bounds__(64, 2) void prefill_f32_kernel(PlanDev pd, const fl
     vk = min(vk, last_limit);
     while (vk >= b + n) {
       b += n;
-      if (++r < w.n_ranges) {
-        const KeyRange kr = pd.ranges[w.range_off + r];
-        t = kr.tok_start;
-        n = kr.len;
-      } else {
-        t = w.tok_start;
-        n = 0x7fffffff - b;
-      }
+      const KeyRange kr = range(++r, b);
+      t = kr.tok_start;
+      n = kr.len;
     }
     return t + (vk - b);
   };

@@ -52,3 +52,8 @@ def test_decode_loads_are_global(kernels):
 def test_decode_keeps_its_registers(kernels):
     for name, code in _named(kernels, "decode").items():
         assert not [c for c in code if c.startswith("scratch_")], name
+
+
+def test_fp32_prefill_keeps_its_registers(kernels):
+    for name, code in _named(kernels, "prefill_f32").items():
+        assert not [c for c in code if c.startswith(("scratch_", "flat_load"))], name
