@@ -109,7 +109,7 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_bf16_kernel(PlanDev pd, co
   __shared__ __attribute__((aligned(256))) float Pq[64];                     // positions of the rows of the Q tile in flight
   __shared__ __attribute__((aligned(16))) WorkItem s_items[kItemBatch];
   // first ancestor ranges of each staged item as {delta, end}: virtual keys from the end of the entry before up to `end`
-  // are the tokens delta + key
+  // are the tokens delta + key; entries behind the last range stand for the own run
   __shared__ __attribute__((aligned(8))) int2 s_ranges[MANY ? kItemBatch : 1][kRangeCache];
   auto fK = [](int row) { return (row / RPC) % CPR; };
   auto fV = [](int row) { return 4 * ((row / RPC) % (CPR / 4)); };
@@ -217,29 +217,29 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_bf16_kernel(PlanDev pd, co
       int tok0 = -1, end = 0, delta = 0, next_end = 0, next_delta = 0;
       if (vk0 >= w.anc_keys) {
         if (vk0 + BK <= w.anc_keys + w.row0 + w.n_rows) tok0 = w.tok_start + (vk0 - w.anc_keys);
-      } else if (vk0 + BK <= w.anc_keys) {
-        if (!MANY || w.n_ranges == 1) {
-          tok0 = w.r0_start + vk0;
-        } else if (w.n_ranges <= kRangeCache) {
-          // several ancestor ranges (cached paths, chains of kept documents): one lane per range finds the one that holds
-          // the stage's first key.  (A loop over the ranges, one LDS round trip each, cost 12 % of a launch behind a
-          // chain of four documents: 414 us, now 364.)
-          const int2 kr = s_ranges[local][lane % kRangeCache];
-          const int r = __builtin_ctz(uint32_t(__ballot(vk0 < kr.y)) | 1u << (kRangeCache - 1));
-          end = __builtin_amdgcn_readlane(kr.y, r);
-          delta = __builtin_amdgcn_readlane(kr.x, r);
-          if (vk0 + BK <= end) {
-            tok0 = delta + vk0;
-          } else if (r + 1 < kRangeCache) {
-            // the stage reaches into the next range (the last one ends behind it: it ends within the ancestors)
-            next_end = __builtin_amdgcn_readlane(kr.y, r + 1);
-            next_delta = __builtin_amdgcn_readlane(kr.x, r + 1);
-          }
+      } else if (!MANY || w.n_ranges == 1) {
+        if (vk0 + BK <= w.anc_keys) tok0 = w.r0_start + vk0;
+      } else if (w.n_ranges <= kRangeCache) {
+        // several ancestor ranges (cached paths, chains of kept documents): one lane per range finds the one that holds
+        // the stage's first key.  (A loop over the ranges, one LDS round trip each, cost 12 % of a launch behind a
+        // chain of four documents: 414 us, now 364.)
+        const int2 kr = s_ranges[local][lane % kRangeCache];
+        const int r = __builtin_ctz(uint32_t(__ballot(vk0 < kr.y)) | 1u << (kRangeCache - 1));
+        end = __builtin_amdgcn_readlane(kr.y, r);
+        delta = __builtin_amdgcn_readlane(kr.x, r);
+        if (vk0 + BK <= end) {
+          tok0 = delta + vk0;
+        } else if (r + 1 < kRangeCache) {
+          // the stage reaches into the next range or, behind the last one, into the own run
+          next_end = __builtin_amdgcn_readlane(kr.y, r + 1);
+          next_delta = __builtin_amdgcn_readlane(kr.x, r + 1);
         }
       }
       const bool two = MANY && next_end >= vk0 + BK;                // two ranges hold the stage: no search per lane
       auto stage_tok = [&](int vk) -> int {
-        return two ? (vk < end ? delta : next_delta) + vk : map_tok(w, local, vk);
+        if (!two) return map_tok(w, local, vk);
+        vk = min(vk, w.anc_keys + w.row0 + w.n_rows - 1);     // past the end, as in map_tok
+        return (vk < end ? delta : next_delta) + vk;
       };
       const uint64_t hoff = (uint64_t)(uint32_t)w.kv_head * kv_hs * 2;
       if (tok0 >= 0) {
@@ -303,11 +303,15 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_bf16_kernel(PlanDev pd, co
     for (int i = tid; MANY && i < (it_end - it) * kRangeCache; i += T) {
       const int li = i / kRangeCache, r = i % kRangeCache;
       const int n_rng = s_items[li].n_ranges;
-      if (n_rng > 1 && r < n_rng) {
-        int begin = 0;
-        for (int j = 0; j < r; ++j) begin += pd.ranges[s_items[li].range_off + j].len;
-        const KeyRange kr = pd.ranges[s_items[li].range_off + r];
-        s_ranges[li][r] = int2{kr.tok_start - begin, begin + kr.len};
+      if (n_rng > 1) {
+        int2 e = {s_items[li].tok_start - s_items[li].anc_keys, 0x7fffffff};
+        if (r < n_rng) {
+          int begin = 0;
+          for (int j = 0; j < r; ++j) begin += pd.ranges[s_items[li].range_off + j].len;
+          const KeyRange kr = pd.ranges[s_items[li].range_off + r];
+          e = {kr.tok_start - begin, begin + kr.len};
+        }
+        s_ranges[li][r] = e;
       }
     }
     land_and_sync(0);
