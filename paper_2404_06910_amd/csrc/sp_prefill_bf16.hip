@@ -358,75 +358,26 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_bf16_kernel(PlanDev pd, co
           pos_q = Pq[my_row];
         }
       } else {
-        // one block of 32 keys
-        auto block = [&](const int sub) {
-          const int vk0 = st * BK + 32 * sub;
-          f32x16 s;
+        // Blocks of 32 keys; those entirely above this wave's diagonal are not computed.  At 128 dims the block is a function
+        // that is optimised by itself before it becomes part of the loop: that takes fewer registers, which there decides
+        // between spilling and not (iterative round of 32 heads 376 -> 367 us).  At 64 dims, where there are enough, its
+        // schedule is the worse one (iterative round of 32/8 heads with bias, ragged: 219.7 us in place, 234.8 as a function).
+        if constexpr (D == 128) {
+          auto block = [&](const int sub) {
+            const int vk0 = st * BK + 32 * sub;
+#include "sp_prefill_block.inc"
+          };
 #pragma unroll
-          for (int i = 0; i < 16; ++i) s[i] = 0.f;
-          const unsigned char *krow = sl + (32 * sub + l32) * ROWB;
+          for (int sub = 0; sub < BK / 32; ++sub)
+            if (active && st * BK + 32 * sub <= wave_last) block(sub);
+        } else {
 #pragma unroll
-          for (int j = 0; j < NJ; ++j) {
-            const bf16x8 a = *reinterpret_cast<const bf16x8 *>(krow + ((((2 * j) ^ kf_fh) | kf_lo) * 16));
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[j], s, 0, 0, 0);
+          for (int sub = 0; sub < BK / 32; ++sub) {
+            const int vk0 = st * BK + 32 * sub;
+            if (!active || vk0 > wave_last) continue;
+#include "sp_prefill_block.inc"
           }
-
-          // scores in log2 units: t = s * scale2 (+ bias); masked entries -> -inf
-          if (BIAS) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-              s[i] = fmaf(s[i], scale2, slope2 * (Ps[buf][32 * sub + 8 * (i / 4) + 4 * half + (i % 4)] - pos_q));
-          }
-          if (vk0 + 31 > wave_first_limit) {                 // diagonal block: some rows see only part of it
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-              if (vk0 + 8 * (i / 4) + 4 * half + (i % 4) > my_limit) s[i] = -INFINITY;
-          }
-          float mx = fmaxf(s[0], s[1]);
-#pragma unroll
-          for (int i = 2; i < 16; ++i) mx = fmaxf(mx, s[i]);
-          if (!BIAS) mx *= scale2;                           // scale2 > 0: max commutes with the scaling
-          mx = xhalf_max(mx);
-          // The reference maximum is allowed to lag by up to 8 (factor 256 in p), which fp32 sums and
-          // bf16 P absorb; the accumulator registers are rescaled only when some row exceeds that.
-          if (__any(mx > m_run + 8.f)) {
-            const float m_new = fmaxf(m_run, mx);
-            const float alpha = fast_exp2(m_run - m_new);
-            m_run = m_new;
-            l_run *= alpha;
-#pragma unroll
-            for (int c = 0; c < NC; ++c)
-#pragma unroll
-              for (int i = 0; i < 16; ++i) o[c][i] *= alpha;
-          }
-          float ls = 0.f;
-          bf16x8 pb[2];
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const float p = BIAS ? fast_exp2(s[i] - m_run) : fast_exp2(fmaf(s[i], scale2, -m_run));
-            ls += p;
-            pb[i / 8][i % 8] = static_cast<__bf16>(p);
-          }
-          l_run += ls;
-          // V^T fragments through the LDS transpose read (4 keys x 16 dims per 16-lane group)
-          const unsigned char *vrow = sl + HALFB + (32 * sub + 4 * half + tr_row) * ROWB + tr_sub8;
-#pragma unroll
-          for (int c = 0; c < NC; ++c) {
-            const int choff = (((4 * c) ^ tr_f) + tr_chlo) * 16;
-#pragma unroll
-            for (int mm = 0; mm < 2; ++mm) {
-              const unsigned char *vp = vrow + 16 * mm * ROWB + choff;
-              const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4 *)vp);
-              const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4 *)(vp + 8 * ROWB));
-              const bf16x8 a = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-              o[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[mm], o[c], 0, 0, 0);
-            }
-          }
-        };
-        // blocks entirely above this wave's diagonal are not computed
-#pragma unroll
-        for (int sub = 0; sub < BK / 32; ++sub)
-          if (active && st * BK + 32 * sub <= wave_last) block(sub);
+        }
 
         if (last_stage) {
           // Epilogue of the item.  O^T sits in registers one query row per lane; it is transposed
