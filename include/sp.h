@@ -27,8 +27,8 @@
  *   Decode launches that cut their key lists into pieces use scratch memory of the plan, one region per stream, and per
  *   stream of each graph capture, that has launched a decode of the plan since it was made or updated.  The first
  *   regions come with the plan's tables, further ones are allocated when they are first needed (also under capture; up
- *   to 256).  A launch that gets none (the 257th, or on hipStreamPerThread) gives the same bits, slower: one workgroup
- *   then does the pieces in turn.  The regions are given back with the plan's tables.  Hence: replays of one captured
+ *   to 256).  A launch that gets none (of the 257th stream or capture) gives the same bits, slower: one workgroup then
+ *   does the pieces in turn.  The regions are given back with the plan's tables.  Hence: replays of one captured
  *   decode must not overlap each other; after sp_plan_update, a graph captured before must not run beside other decodes
  *   of the plan; and a stream must have finished its decodes before it is destroyed.
  */

@@ -1,6 +1,7 @@
 // Host side of libsp.so: contexts, plan construction (validation, ancestor chains, tile work
 // list, decode gather tables), argument checks and kernel dispatch.  No kernels live here.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -231,15 +232,19 @@ static bool more_decode_regions(const sp_plan *p) {
   p->dec_blocks.push_back({block, bytes});
   for (size_t i = 0; i < n; ++i)
     p->dec_regions.push_back({static_cast<char *>(block) + n * p->dec_count_bytes + i * p->dec_part_bytes,
-                              reinterpret_cast<uint32_t *>(static_cast<char *>(block) + i * p->dec_count_bytes), nullptr, 0, false});
+                              reinterpret_cast<uint32_t *>(static_cast<char *>(block) + i * p->dec_count_bytes), nullptr, 0, 0,
+                              false});
   return true;
 }
 
-// The region of the order of execution that a launch on `s` joins.  hipStreamPerThread names another stream in every
-// thread and gets none.  Errors are dealt with here: the launch that follows reports its own.
+// The region of the order of execution that a launch on `s` joins.  Errors are dealt with here: the launch that follows
+// reports its own.
 const sp::DecodeRegion *sp::decode_region(const sp_plan *p, hipStream_t s) {
-  if (s == hipStreamPerThread || p->dec_regions.empty()) return nullptr;
-  unsigned long long order = 0;
+  if (p->dec_regions.empty()) return nullptr;
+  static std::atomic<unsigned long long> threads{0};
+  thread_local const unsigned long long this_thread = ++threads;
+  const unsigned long long thread = s == hipStreamPerThread ? this_thread : 0;   // that name is another stream in every thread
+  unsigned long long capture = 0;
   if (s) {                                              // the null stream cannot be captured
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     unsigned long long id = 0;
@@ -247,11 +252,11 @@ const sp::DecodeRegion *sp::decode_region(const sp_plan *p, hipStream_t s) {
       (void)hipGetLastError();
       return nullptr;
     }
-    if (st != hipStreamCaptureStatusNone) order = id + 1;
+    if (st != hipStreamCaptureStatusNone) capture = id + 1;
   }
   DecodeRegion *unused = nullptr;
   for (DecodeRegion &r : p->dec_regions) {
-    if (r.taken && r.stream == s && r.order == order) return &r;
+    if (r.taken && r.stream == s && r.capture == capture && r.thread == thread) return &r;
     if (!r.taken && !unused) unused = &r;
   }
   if (!unused) {
@@ -263,7 +268,8 @@ const sp::DecodeRegion *sp::decode_region(const sp_plan *p, hipStream_t s) {
     unused = &p->dec_regions[have];
   }
   unused->stream = s;
-  unused->order = order;
+  unused->capture = capture;
+  unused->thread = thread;
   unused->taken = true;
   return unused;
 }
@@ -690,7 +696,7 @@ sp_status upload_plan(sp_ctx *ctx, sp_plan *p, void *reuse_blob, size_t reuse_by
   p->dec_in_blob = n_regions;
   for (size_t i = 0; i < n_regions; ++i)
     p->dec_regions.push_back({base + o_part + i * p->dec_part_bytes,
-                              reinterpret_cast<uint32_t *>(base + o_count + i * p->dec_count_bytes), nullptr, 0, false});
+                              reinterpret_cast<uint32_t *>(base + o_count + i * p->dec_count_bytes), nullptr, 0, 0, false});
   return SP_OK;
 }
 

@@ -48,8 +48,9 @@ constexpr int kDecFirstRegions = 4, kDecPlanRegions = 32, kDecMaxRegions = 256;
 struct DecodeRegion {
   void *part;
   uint32_t *count;
-  hipStream_t stream;             // owner: a stream, or a stream within one capture (order = capture id + 1, else 0)
-  unsigned long long order;
+  // owner: a stream (hipStreamPerThread: of one thread), or a stream within one capture
+  hipStream_t stream;
+  unsigned long long capture, thread;     // capture id + 1; number of the thread; else 0
   bool taken;
 };
 

@@ -1,6 +1,6 @@
 """sp_pruned_decode where the key lists are long enough to be cut into pieces, and the grouped-head kernel: against the
 oracle, at key counts on and around the piece and tile boundaries, with every head grouping the dispatch knows; and the
-scratch regions of the pieces: streams do not share one, and a launch that gets none agrees bit for bit."""
+scratch regions of the pieces: streams do not share one."""
 import math
 
 import numpy as np
@@ -116,9 +116,9 @@ def test_more_ranges_than_a_wave_has_lanes(ctx, Hq, Hkv):
     _check(got.float().cpu().numpy(), x, st, [9], "bf16")
 
 
-def test_streams_have_their_own_scratch_and_going_without_changes_nothing():
+def test_streams_have_their_own_scratch():
     """One plan, 20 streams: overlapping launches on all of them give what a lone launch gives, bit for bit, and so do
-    launches on the per-thread stream, which get no scratch."""
+    launches on the per-thread stream."""
     print("case: decode on 20 streams of one plan", flush=True)
     ctx = B.Context(0)
     rng = np.random.default_rng(4)

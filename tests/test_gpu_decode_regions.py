@@ -1,6 +1,8 @@
 """Scratch of the decode launches that cut their key lists into pieces: every stream and every capture of a plan gets a region
 of its own, however many there are and have been, and gives it back with the plan.  A captured launch tells by its grid
 whether it got one: a workgroup per piece, in y."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -52,6 +54,52 @@ def test_every_capture_of_a_plan_gets_a_region():
         assert torch.equal(o, want)
     for g in graphs:
         g.destroy()
+    x["plan"].close()
+    ctx.close()
+
+
+def test_the_last_region_and_going_without():
+    """256 regions to a plan, one of them the eager stream's: later captures go without, which changes no bit."""
+    ctx = B.Context(0)
+    x, o = _plan(ctx, 2)
+    want = _decode(ctx, x, "bf16").clone()
+    torch.cuda.synchronize()
+    stream = torch.cuda.Stream()
+    graphs = [_captured(ctx, x, o, stream) for _ in range(260)]
+    ys = [g.grids()[0][1] for g in graphs]
+    assert ys[0] > 1 and ys == [ys[0]] * 255 + [1] * 5
+    for i in (254, 255, 259):
+        print("replay", i, flush=True)
+        o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graphs[i].replay()
+        torch.cuda.synchronize()
+        assert torch.equal(o, want)
+    for g in graphs:
+        g.destroy()
+    x["plan"].close()
+    ctx.close()
+
+
+def test_the_per_thread_stream_of_every_thread():
+    """hipStreamPerThread names another stream in each host thread: launches of several threads, one after the other."""
+    ctx = B.Context(0)
+    x, o = _plan(ctx, 3)
+    want = _decode(ctx, x, "bf16").clone()
+    torch.cuda.synchronize()
+    ctx.sp_set_stream(2)                                     # hipStreamPerThread
+    outs = [torch.full_like(o, float("nan")) for _ in range(6)]
+
+    def work(out):
+        for _ in range(4):
+            _decode(ctx, x, "bf16", out)
+    torch.cuda.synchronize()
+    for out in outs:
+        t = threading.Thread(target=work, args=(out,))
+        t.start()
+        t.join()
+    torch.cuda.synchronize()
+    assert all(torch.equal(out, want) for out in outs)
     x["plan"].close()
     ctx.close()
 
