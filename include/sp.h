@@ -14,8 +14,9 @@
  *   Every entry point returns sp_status; arguments and tables are validated on the host before
  *   any kernel launch; nothing is printed; sp_last_error() returns the detail of the last
  *   failure on that context.  Kernels are enqueued on the context's HIP stream and the call
- *   returns without synchronising.  No floating-point atomics are used: equal inputs give
- *   bit-identical outputs.  Supported: head_dim 64 or 128; dtype fp32 or bf16 (storage of
+ *   returns without synchronising.  No floating-point atomics are used: equal calls give
+ *   bit-identical outputs.  (A decode cuts key lists into pieces by the sizes of the whole call, so a prompt's
+ *   output may round differently alone and in a batch, see sp_pruned_decode.)  Supported: head_dim 64 or 128; dtype fp32 or bf16 (storage of
  *   Q/K/V/O and logits; all arithmetic accumulates in fp32); n_q_heads a multiple of
  *   n_kv_heads (query head h reads KV head h / (n_q_heads / n_kv_heads)).
  *   Threads: a context (and the plans made on it) is used by one host thread at a time;
@@ -190,7 +191,7 @@ sp_status sp_path_saliency(sp_ctx *ctx, const void *logits, sp_dtype dtype, int6
 /*
  * sp_path_saliency for callers that cannot allocate device memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): same arguments, same result, but the scratch
- * memory of the kernels (one log-likelihood per row, the per-path accumulators) is a static device array
+ * memory of the kernels (one record per row or piece of a row, the per-path accumulators) is a static device array
  * of the library, 1.25 MiB per GPU, held until the process ends, instead of the context's workspace, and
  * the call makes no hipMalloc / hipFree.  Limits: n_rows <= 65536 and n_path_slots <= 16384, else
  * SP_ERR_UNSUPPORTED.  The array is shared by every call on that GPU: calls that overlap in time on one
@@ -227,6 +228,9 @@ sp_status sp_prune_topk(sp_ctx *ctx, const float *score, const int32_t *path_off
  * resp_len: DEVICE int32 [n_prompts] or NULL (= zeros); new_pos: DEVICE fp32 [n_prompts] or NULL;
  * q_new, o_out: DEVICE [n_prompts, n_q_heads, head_dim]; k_new, v_new: DEVICE [n_prompts,
  * n_kv_heads, head_dim].  Contract: len_b < resp_capacity (rows beyond are dropped, not written).
+ * Rounding: the order in which a prompt's keys are summed depends on n_prompts, the head counts, the longest shared part and
+ * path of any prompt of the plan, k, resp_len_add and, where resp_len is given, resp_capacity; not on the stream, on
+ * captures or on launches beside it.  Two calls that differ in these may differ by the rounding of fp32 sums.
  */
 sp_status sp_pruned_decode(sp_ctx *ctx, const sp_plan *plan, const int32_t *kept, int32_t k,
                            const void *K_prefill, const void *V_prefill, int64_t kv_tok_stride,

@@ -193,7 +193,7 @@ extern "C" sp_status sp_set_stream(sp_ctx *ctx, void *hip_stream) {
   return SP_OK;
 }
 
-// Saliency workspace (per-row log-likelihoods, per-slot accumulators).  A block that is too small is
+// Saliency workspace (a record per row or piece of a row, per-slot accumulators).  A block that is too small is
 // replaced and kept until sp_destroy (a captured graph may still name it); nothing is ever freed inside a
 // hot call, and the usual sizes never allocate: the block made in sp_create covers 65536 rows.
 static sp_status ensure_sal(sp_ctx *ctx, int64_t n_rows, int32_t n_slots) {

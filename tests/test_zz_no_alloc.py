@@ -43,15 +43,21 @@ def test_static_scratch_entry_point_matches_the_allocating_one():
         assert np.array_equal(got_a, got_b), (got_a, got_b)
         ref = orc.path_saliency(x, tgt, rp, n, prior=prior, mode="mean" if mode == B.SALIENCY_MEAN else "sum")
         np.testing.assert_allclose(got_b, ref, rtol=1e-3, atol=1e-5)
-    # many slots and rows scattered over them: per-lane atomics into the static array's accumulators
-    R, n, vocab = 96, 5000, 520
-    x, tgt, rp, prior = _case(rng, R, n, vocab, "f32")
-    X, T, P = dev(x, "f32"), dev(tgt), dev(rp)
-    for _ in range(2):                                          # twice: the accumulators must come back to zero
-        b = torch.full((n,), float("nan"), device="cuda")
-        ctx.sp_path_saliency_static(X, T, P, n, b)
-        torch.cuda.synchronize()
-        np.testing.assert_allclose(b.cpu().numpy(), orc.path_saliency(x, tgt, rp, n), rtol=1e-3, atol=1e-5)
+    # rows scattered over many slots.  96 rows: one workgroup per slot scans them.  5000 rows of 300 slots and 300 rows of
+    # 16384: integer atomics into the static array's accumulators, lane by lane where a wave holds more than four slots.
+    for R, n, vocab in ((96, 5000, 520), (5000, 300, 64), (300, 16384, 64), (7000, 16384, 64)):
+        print("case:", R, n, vocab, flush=True)
+        x, tgt, rp, prior = _case(rng, R, n, vocab, "f32")
+        X, T, P = dev(x, "f32"), dev(tgt), dev(rp)
+        ref = orc.path_saliency(x, tgt, rp, n)
+        first = None
+        for _ in range(3):                                      # the accumulators must come back to zero
+            b = torch.full((n,), float("nan"), device="cuda")
+            ctx.sp_path_saliency_static(X, T, P, n, b)
+            torch.cuda.synchronize()
+            np.testing.assert_allclose(b.cpu().numpy(), ref, rtol=1e-3, atol=1e-5)
+            assert first is None or torch.equal(b, first)
+            first = b
     # beyond the static maximum: a clear error, nothing launched
     n_big = 16384 + 1
     with pytest.raises(B.SpError) as e:
