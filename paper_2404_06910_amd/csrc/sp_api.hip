@@ -163,7 +163,9 @@ extern "C" sp_status sp_create(sp_ctx **out, int device, void *hip_stream) {
 }
 
 static void ctx_unref(sp_ctx *ctx) {
-  if (--ctx->refs == 0) delete ctx;
+  if (--ctx->refs) return;
+  for (void *p : ctx->dec_chunks) (void)hipFree(p);
+  delete ctx;
 }
 
 extern "C" void sp_destroy(sp_ctx *ctx) {
@@ -591,6 +593,36 @@ sp_status build_plan(sp_ctx *ctx, const sp_segtable *t, int32_t n_q_heads, int32
   return SP_OK;
 }
 
+// At least `bytes` of the context's decode chunks: the smallest piece of a plan that is gone that holds them, else the next of
+// the current chunk, else a new chunk.
+bool take_scratch(sp_ctx *ctx, size_t bytes, void **out, size_t *out_bytes) {
+  auto &pieces = ctx->dec_free;
+  size_t best = pieces.size();
+  for (size_t i = 0; i < pieces.size(); ++i)
+    if (pieces[i].second >= bytes && (best == pieces.size() || pieces[i].second < pieces[best].second)) best = i;
+  if (best < pieces.size()) {
+    *out = pieces[best].first;
+    *out_bytes = pieces[best].second;
+    pieces.erase(pieces.begin() + best);
+    return true;
+  }
+  bytes = (bytes + 255) & ~size_t(255);
+  if (ctx->dec_left < bytes) {
+    const size_t chunk = std::max(bytes, sp::kDecChunkBytes);
+    void *p = nullptr;
+    if (hipMalloc(&p, chunk) != hipSuccess) return false;
+    ctx->dec_chunks.push_back(p);
+    if (ctx->dec_left) pieces.push_back({ctx->dec_at, ctx->dec_left});
+    ctx->dec_at = static_cast<char *>(p);
+    ctx->dec_left = chunk;
+  }
+  *out = ctx->dec_at;
+  *out_bytes = bytes;
+  ctx->dec_at += bytes;
+  ctx->dec_left -= bytes;
+  return true;
+}
+
 // Device copy of a plan's tables: every table is laid out in the context's pinned staging buffer and
 // leaves in ONE asynchronous copy on the context's stream, into a device block taken from the blocks
 // of destroyed plans when one is large enough (no hipMalloc / hipFree per request).  Work enqueued on
@@ -622,11 +654,15 @@ sp_status upload_plan(sp_ctx *ctx, sp_plan *p, void *reuse_blob, size_t reuse_by
                o_sd = add(shared_desc.data(), shared_desc.size() * sizeof(sp::RangeDesc)),
                o_pd = add(path_desc.data(), path_desc.size() * sizeof(sp::RangeDesc)),
                o_dr = add(p->dec_ranges.data(), p->dec_ranges.size() * sizeof(sp::KeyRange));
-  // decode regions: their counters travel with the tables (as zeros), the partial sums lie behind all that travels
+  // decode regions: their counters travel with the tables (as zeros), their partial sums come from the context's chunks
   const size_t n_regions = p->dec_part_bytes ? size_t(ctx->dec_regions) : 0;
-  const size_t o_count = (off + 255) & ~size_t(255), o_part = o_count + n_regions * p->dec_count_bytes + 256;
-  const size_t upload = o_part, total = o_part + n_regions * p->dec_part_bytes;
+  const size_t o_count = (off + 255) & ~size_t(255), total = o_count + n_regions * p->dec_count_bytes + 256;
   SP_HIP(ctx, hipSetDevice(ctx->device));
+  void *scratch = p->dec_scratch;
+  size_t scratch_bytes = p->dec_scratch_bytes;
+  const bool new_scratch = scratch_bytes < n_regions * p->dec_part_bytes;
+  if (new_scratch && !take_scratch(ctx, n_regions * p->dec_part_bytes, &scratch, &scratch_bytes))
+    return fail(&ctx->err, SP_ERR_WORKSPACE, "could not allocate %zu bytes of decode scratch", n_regions * p->dec_part_bytes);
   // device block: the plan's own (an update), else the smallest pooled block that fits, else a new one
   void *blob = nullptr;
   size_t blob_bytes = 0;
@@ -642,22 +678,27 @@ sp_status upload_plan(sp_ctx *ctx, sp_plan *p, void *reuse_blob, size_t reuse_by
       ctx->blob_pool.erase(ctx->blob_pool.begin() + best);
     } else {
       blob_bytes = ((total + total / 4) + 65535) & ~size_t(65535);      // headroom: the next table may be larger
-      if (hipMalloc(&blob, blob_bytes) != hipSuccess)
+      if (hipMalloc(&blob, blob_bytes) != hipSuccess) {
+        if (new_scratch) ctx->dec_free.push_back({scratch, scratch_bytes});
         return fail(&ctx->err, SP_ERR_WORKSPACE, "could not allocate %zu bytes for the plan's tables", blob_bytes);
+      }
     }
   }
-  auto give_back = [&]() { if (blob != reuse_blob) ctx->blob_pool.push_back({blob, blob_bytes}); };
+  auto give_back = [&]() {
+    if (blob != reuse_blob) ctx->blob_pool.push_back({blob, blob_bytes});
+    if (new_scratch) ctx->dec_free.push_back({scratch, scratch_bytes});
+  };
   // staging buffer: wait until the previous upload has left it, grow if needed
   if (ctx->stage_busy) {
     hipError_t e = hipEventSynchronize(ctx->stage_ev);
     if (e != hipSuccess) { give_back(); return fail(&ctx->err, SP_ERR_HIP, "plan upload: %s", hipGetErrorString(e)); }
     ctx->stage_busy = false;
   }
-  if (ctx->stage_bytes < upload) {
+  if (ctx->stage_bytes < total) {
     if (ctx->stage) (void)hipHostFree(ctx->stage);
     ctx->stage = nullptr;
     ctx->stage_bytes = 0;
-    const size_t want = std::max(upload + upload / 4, size_t(1) << 20);
+    const size_t want = std::max(total + total / 4, size_t(1) << 20);
     if (hipHostMalloc(&ctx->stage, want, hipHostMallocDefault) != hipSuccess) {
       give_back();
       return fail(&ctx->err, SP_ERR_WORKSPACE, "could not allocate %zu bytes of pinned staging memory", want);
@@ -668,7 +709,7 @@ sp_status upload_plan(sp_ctx *ctx, sp_plan *p, void *reuse_blob, size_t reuse_by
   for (auto &pc : pieces)
     if (pc.bytes) std::memcpy(stg + pc.at, pc.src, pc.bytes);
   if (n_regions) std::memset(stg + o_count, 0, n_regions * p->dec_count_bytes);
-  hipError_t e = hipMemcpyAsync(blob, stg, upload, hipMemcpyHostToDevice, ctx->stream);
+  hipError_t e = hipMemcpyAsync(blob, stg, total, hipMemcpyHostToDevice, ctx->stream);
   if (e == hipSuccess) e = hipEventRecord(ctx->stage_ev, ctx->stream);
   if (e != hipSuccess) { give_back(); return fail(&ctx->err, SP_ERR_HIP, "plan upload: %s", hipGetErrorString(e)); }
   ctx->stage_busy = true;
@@ -692,10 +733,15 @@ sp_status upload_plan(sp_ctx *ctx, sp_plan *p, void *reuse_blob, size_t reuse_by
   d.n_tokens = p->n_tokens;
   d.n_prompts = p->n_prompts;
   d.n_q_heads = p->n_q_heads; d.n_kv_heads = p->n_kv_heads; d.head_dim = p->head_dim;
+  if (new_scratch) {
+    if (p->dec_scratch) ctx->dec_free.push_back({p->dec_scratch, p->dec_scratch_bytes});
+    p->dec_scratch = scratch;
+    p->dec_scratch_bytes = scratch_bytes;
+  }
   p->dec_regions.clear();
-  p->dec_in_blob = n_regions;
+  p->dec_first = n_regions;
   for (size_t i = 0; i < n_regions; ++i)
-    p->dec_regions.push_back({base + o_part + i * p->dec_part_bytes,
+    p->dec_regions.push_back({static_cast<char *>(scratch) + i * p->dec_part_bytes,
                               reinterpret_cast<uint32_t *>(base + o_count + i * p->dec_count_bytes), nullptr, 0, 0, false});
   return SP_OK;
 }
@@ -746,11 +792,13 @@ extern "C" sp_status sp_plan_update(sp_plan *plan, const sp_segtable *t) {
     // them is ordered behind those kernels on the same stream.
     fresh.dev_blob = plan->dev_blob;
     fresh.dev_blob_bytes = plan->dev_blob_bytes;
+    fresh.dec_scratch = plan->dec_scratch;
+    fresh.dec_scratch_bytes = plan->dec_scratch_bytes;
     st = upload_plan(ctx, &fresh, plan->dev_blob, plan->dev_blob_bytes);
     if (st != SP_OK) { fresh.dev_blob = nullptr; return st; }
   }
   if (fresh.dec_part_bytes == plan->dec_part_bytes && fresh.dec_count_bytes == plan->dec_count_bytes) {
-    for (size_t i = plan->dec_in_blob; i < plan->dec_regions.size(); ++i) {
+    for (size_t i = plan->dec_first; i < plan->dec_regions.size(); ++i) {
       fresh.dec_regions.push_back(plan->dec_regions[i]);
       fresh.dec_regions.back().taken = false;
     }
@@ -768,6 +816,7 @@ extern "C" void sp_plan_destroy(sp_plan *plan) {
   sp_ctx *ctx = plan->ctx;
   if (plan->dev_blob) give_back_block(ctx, plan->dev_blob, plan->dev_blob_bytes);
   drop_decode_blocks(ctx, plan);
+  if (plan->dec_scratch) ctx->dec_free.push_back({plan->dec_scratch, plan->dec_scratch_bytes});
   delete plan;
   if (ctx) ctx_unref(ctx);
 }

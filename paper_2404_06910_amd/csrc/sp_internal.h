@@ -42,9 +42,10 @@ constexpr size_t kSalStaticBytes = 256 + size_t(kSalStaticRows) * sizeof(RowPart
 // row, piece) pairs plus {max, sum} each, and at most kDecPartCounters arrival counters (zero between launches).
 constexpr int64_t kDecPartRows = 4096;
 constexpr int kDecPartCounters = 1024;
-// Regions that a plan's device block holds from the start (or as many as the plan destroyed last had in use, up to
-// kDecPlanRegions), and the most that a plan may come to have.
+// Regions that a plan has from the start (or as many as the plan destroyed last had in use, up to kDecPlanRegions), and the
+// most that a plan may come to have.
 constexpr int kDecFirstRegions = 4, kDecPlanRegions = 32, kDecMaxRegions = 256;
+constexpr size_t kDecChunkBytes = size_t(16) << 20;
 struct DecodeRegion {
   void *part;
   uint32_t *count;
@@ -132,6 +133,13 @@ struct sp_ctx {
   bool stage_busy = false;
   std::vector<std::pair<void *, size_t>> blob_pool;
   int dec_regions = sp::kDecFirstRegions;   // decode regions that the next plan starts with
+  // Memory for the partial sums of plans' first regions: chunks, cut up as plans ask (a hipMalloc of a few MB per plan would
+  // double the time to make one), and the pieces of plans that are gone.  Freed with the last plan, since a captured decode
+  // may be replayed until then.
+  std::vector<void *> dec_chunks;
+  char *dec_at = nullptr;
+  size_t dec_left = 0;
+  std::vector<std::pair<void *, size_t>> dec_free;
   int refs = 1;               // the context itself + every live plan made on it
   bool closed = false;        // sp_destroy was called; the struct lives on until the last plan is gone
 };
@@ -164,14 +172,17 @@ struct sp_plan {
   std::vector<int32_t> path_max_ranges;  // per prompt: max ranges of any single path
   std::vector<float> pos, slopes;        // copies of tok_pos / alibi_slopes (empty when not given)
   // Decode scratch (sp::DecodeRegion).  A region belongs to one order of execution -- a stream, or a stream within one
-  // capture -- until the plan is updated or destroyed, so that launches that may overlap never share one.  The regions
-  // follow the tables in the plan's device block, further ones come in blocks of their own; all go the way of the tables:
-  // whoever gets the memory next has work ordered behind the plan's, as sp_plan_update and sp_plan_destroy require.
+  // capture -- until the plan is updated or destroyed, so that launches that may overlap never share one.  The first
+  // regions' counters lie behind the tables in the plan's device block and their partial sums in the context's chunks,
+  // further regions come in blocks of their own; all go the way of the tables: whoever gets the memory next has work ordered
+  // behind the plan's, as sp_plan_update and sp_plan_destroy require.
   size_t dec_part_bytes = 0, dec_count_bytes = 0;     // of one region; 0: no decode of this plan is cut into pieces
-  size_t dec_in_blob = 0;                             // regions in the device block; the others are in dec_blocks
+  size_t dec_first = 0;                               // first regions; the others are in dec_blocks
+  void *dec_scratch = nullptr;                        // the first regions' partial sums
+  size_t dec_scratch_bytes = 0;
   mutable std::vector<sp::DecodeRegion> dec_regions;
   mutable std::vector<std::pair<void *, size_t>> dec_blocks;
-  // device copies and decode scratch (one allocation)
+  // device copies (one allocation)
   void *dev_blob = nullptr;
   size_t dev_blob_bytes = 0;  // capacity of the allocation
   sp::PlanDev dev{};
