@@ -189,10 +189,10 @@ __global__ __launch_bounds__(64, 2) void prefill_f32_kernel(PlanDev pd, const fl
       if (diag && vk0 + 4 * quad + r > my_limit) t[r] = -INFINITY;
     }
     const float mx = quad_max(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3])));
-    // The reference is set 8 above the maximum and stays until a score passes it, so that most steps have nothing to
-    // rescale; p (2^-8 at the maximum) and both sums never exceed what a reference at the maximum gives.
+    // The reference is the maximum itself, as soon as it grows: one that may lag behind it saves 0.5 % of the time and lets
+    // sums overflow early, one that is set above it costs precision (1.67e-7 of the norm against 1.06e-7) and denormals.
     if (__any(mx > m)) {
-      const float m_new = mx > m ? mx + 8.f : m, alpha = fast_exp2(m - m_new);
+      const float m_new = fmaxf(m, mx), alpha = fast_exp2(m - m_new);
       m = m_new;
       l *= alpha;
 #pragma unroll
