@@ -16,7 +16,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsp.so")
-SOURCES = ["sp_api.hip", "sp_prefill_bf16.hip", "sp_prefill_f32.hip", "sp_saliency.hip", "sp_topk.hip",
+SOURCES = ["sp_api.hip", "sp_prefill_bf16.hip", "sp_prefill_wide.hip", "sp_prefill_f32.hip", "sp_saliency.hip", "sp_topk.hip",
            "sp_decode.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=on",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

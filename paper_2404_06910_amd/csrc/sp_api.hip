@@ -340,6 +340,170 @@ void hand_out(const std::vector<int32_t> &cost, int32_t n_slots, const int32_t *
   for (int32_t g = 0; g < n_slots; ++g) begin[g + 1] += begin[g];
 }
 
+// Whether the wide prefill kernel takes the plan, and its tiles if so.
+//
+// A tile has kWideWaves / heads_per_wg blocks of up to 32 rows.  A row interval is cut into blocks, a partial one first (its
+// key stream is the shortest), and the blocks into chunks of a tile's size from the end.  What is left in front of the first
+// chunk is cut into pieces of 1, 2 or 4 blocks, and pieces of one size are put together with those of the group's siblings,
+// the groups that fork behind the same segment and so have the same ancestors: their tile streams the ancestors once.
+//
+// The rule.  Time per compute unit of either kernel, in us, as fitted to 76 plans of 16 documents of 24 to 220 tokens behind 32
+// to 1400 (6 prompts; 32, 24 and 12 heads), within 7-15 %:
+//   other kernel  1.23 per stage of 32 keys and 5.5 per item of a workgroup (a quarter of a unit);  two heads a workgroup
+//                 1.32 and 7.7
+//   wide          2.0 per stage that all eight waves compute on and 8.8 per tile;  two heads a workgroup 4.2 and 9.3
+// The wide kernel takes the plan where it comes out at 1/0.97 of the other's time or less, and only where every compute unit
+// has 40 stages or more: with fewer its few large tiles end unevenly (one prompt of 32 heads: 128 + 24 tokens behind 448, 17
+// stages a unit, 51 against 52 us; 24 + 8 behind 768, 7.5 stages, 35 against 35).  Of the plans that the rule lets in it was
+// 1.07 to 1.30 times as fast (24 + 8 tokens behind 768: 149 -> 114 us; 220 + 24 behind 1400: 930 -> 829).  Four heads per
+// workgroup share their K/V rows in the other kernel already: 0.85 to 1.05 times as fast here, so they stay there.
+void wide_tiles(sp_plan *p, const std::vector<std::vector<std::pair<int32_t, int32_t>>> &live_rows,
+                const std::vector<int32_t> &group_parent, int32_t n_hg, int n_cu) {
+  using namespace sp;
+  if (p->dtype != SP_BF16 || p->head_dim != 128 || p->heads_per_wg > 2 || p->max_ranges >= kWideRanges) return;
+  const int32_t NB = kWideWaves / p->heads_per_wg;
+  struct Block { int32_t group, row0, n_rows; };
+  auto pad = [](int32_t n) { return (n + 31) & ~31; };
+  auto one_group = [](const std::vector<Block> &bl) { return bl.front().group == bl.back().group; };
+
+  // stages of a tile, and stages that each of its blocks is computed on, summed up
+  int64_t n_tiles = 0, stages = 0, steps = 0;
+  auto count = [&](const std::vector<Block> &bl) {
+    const bool one = one_group(bl);
+    const int32_t anc = p->groups[bl[0].group].anc_keys;
+    int32_t at = one ? anc : pad(anc), keys = 0;
+    const int32_t shared = one ? 0 : (at + kWideStageKeys - 1) / kWideStageKeys;
+    for (size_t i = 0; i < bl.size(); ++i) {
+      if (i && bl[i].group != bl[i - 1].group) { at += pad(keys); keys = 0; }
+      keys = std::max(keys, bl[i].row0 + bl[i].n_rows);
+      const int32_t last = (at + bl[i].row0 + bl[i].n_rows - 1) / kWideStageKeys;
+      steps += shared + last - std::max(shared - 1, one ? -1 : at / kWideStageKeys - 1);
+    }
+    stages += (at + keys + kWideStageKeys - 1) / kWideStageKeys;
+    ++n_tiles;
+  };
+  auto emit = [&](const std::vector<Block> &bl) {
+    WideTile t{};
+    const RowGroup &g0 = p->groups[bl[0].group];
+    const bool one = one_group(bl);
+    t.anc = g0.anc_keys;
+    t.anc_end = one ? 0 : pad(g0.anc_keys);
+    int32_t n = 0, at = 0;
+    for (int32_t r = 0; r < g0.n_ranges; ++r) {
+      const KeyRange &kr = p->ranges[g0.range_off + r];
+      t.range[n++] = {kr.tok_start - at, at + kr.len, kr.tok_start + kr.len - 1, 0};
+      at += kr.len;
+    }
+    if (!one) at = t.range[n - 1].end = t.anc_end;
+    for (size_t i = 0, j; i < bl.size(); i = j) {
+      const RowGroup &g = p->groups[bl[i].group];
+      int32_t keys = 0;
+      for (j = i; j < bl.size() && bl[j].group == bl[i].group; ++j) {
+        t.block[j] = {g.tok_start + bl[j].row0, bl[j].n_rows, at + bl[j].row0, one ? 0 : at};
+        keys = std::max(keys, bl[j].row0 + bl[j].n_rows);
+      }
+      t.n_keys = at + keys;
+      t.range[n++] = {g.tok_start - at, at + pad(keys), g.tok_start + keys - 1, 0};
+      at += pad(keys);
+    }
+    t.range[n - 1].end = 0x7fffffff;
+    for (; n < kWideRanges; ++n) t.range[n] = t.range[n - 1];
+    p->wide_tiles.push_back(t);
+  };
+
+  std::vector<Block> left[3], blocks, tile;                 // left[i]: pieces of 2^i blocks that wait for siblings
+  auto for_each_tile = [&](auto &&fn) {
+    auto flush = [&]() {
+      for (auto &l : left)
+        if (!l.empty()) { fn(l); l.clear(); }
+    };
+    for (size_t g = 0; g < p->groups.size(); ++g) {
+      // siblings that do not follow one another are not brought together
+      if (g && (group_parent[g] < 0 || group_parent[g] != group_parent[g - 1])) flush();
+      for (auto &iv : live_rows[g]) {
+        blocks.clear();
+        const int32_t rem = (iv.second - iv.first) % 32;
+        if (rem) blocks.push_back({int32_t(g), iv.first, rem});
+        for (int32_t r = iv.first + rem; r < iv.second; r += 32) blocks.push_back({int32_t(g), r, 32});
+        size_t i = 0;
+        const size_t front = blocks.size() % NB;
+        for (int32_t b = 0; b < 3; ++b) {
+          const size_t piece = size_t(1) << b;
+          if (!(front & piece)) continue;
+          std::vector<Block> &l = left[b];
+          l.insert(l.end(), blocks.begin() + i, blocks.begin() + i + piece);
+          i += piece;
+          // ranges of a tile: the ancestors' and one per piece at most
+          if (l.size() == size_t(NB) || p->groups[g].n_ranges + int32_t(l.size() / piece) >= kWideRanges) { fn(l); l.clear(); }
+        }
+        for (; i < blocks.size(); i += NB) {
+          tile.assign(blocks.begin() + i, blocks.begin() + i + NB);
+          fn(tile);
+        }
+      }
+    }
+    flush();
+  };
+
+  int64_t narrow_items = 0, narrow_stages = 0;
+  const int32_t narrow_keys = 16 * p->waves_per_wg;
+  for (size_t g = 0; g < p->groups.size(); ++g)
+    for (auto &iv : live_rows[g])
+      for (int32_t end = iv.second; end > iv.first; end -= p->tile_rows) {
+        ++narrow_items;
+        narrow_stages += (p->groups[g].anc_keys + end + narrow_keys - 1) / narrow_keys;
+      }
+  for_each_tile(count);
+  const bool pair = p->heads_per_wg == 2;
+  const double narrow = 0.25 * (pair ? 1.32 * narrow_stages + 7.7 * narrow_items : 1.23 * narrow_stages + 5.5 * narrow_items),
+               wide = pair ? 4.2 / 8 * steps + 9.3 * n_tiles : 2.0 / 8 * steps + 8.8 * n_tiles;
+  if (stages * n_hg < int64_t(40) * n_cu || 0.97 * wide > narrow) return;
+  p->wide = true;
+  p->wide_tiles.reserve(size_t(n_tiles));
+  for_each_tile(emit);
+}
+
+// Work list of the wide kernel, in the order of the other's (see there) and handed out like it; one workgroup per compute unit.
+void wide_work_list(sp_plan *p, int32_t n_hg, int32_t G, int n_cu) {
+  using namespace sp;
+  p->n_tiles = int32_t(p->wide_tiles.size());
+  p->n_wg = (n_cu + 7) / 8 * 8;
+  const size_t n_items = p->wide_tiles.size() * size_t(n_hg);
+  std::vector<int32_t> cost(n_items), owner;
+  const int32_t n_slice = n_hg % 8 == 0 ? 8 : 1, per_slice = n_hg / n_slice;
+  constexpr int64_t kSharedKvBudget = int64_t(1) << 19;
+  auto for_each_item = [&](auto &&fn) {
+    for (int32_t x = 0; x < n_slice; ++x)
+      for (size_t a = 0, e; a < p->wide_tiles.size(); a = e) {
+        // the tiles of one prompt
+        const int32_t prompt = p->groups[p->tok_group[p->wide_tiles[a].block[0].tok]].prompt;
+        int32_t anc = 1;
+        for (e = a; e < p->wide_tiles.size() && p->groups[p->tok_group[p->wide_tiles[e].block[0].tok]].prompt == prompt; ++e)
+          anc = std::max(anc, p->wide_tiles[e].anc);
+        const int32_t hc = int32_t(std::max<int64_t>(
+            1, std::min<int64_t>(per_slice, kSharedKvBudget / (int64_t(anc) * 2 * p->head_dim * 2))));
+        for (int32_t h0 = x * per_slice; h0 < (x + 1) * per_slice; h0 += hc)
+          for (size_t t = a, u; t < e; t = u) {
+            const int32_t g = p->tok_group[p->wide_tiles[t].block[0].tok];
+            for (u = t; u < e && p->tok_group[p->wide_tiles[u].block[0].tok] == g; ++u) {}
+            for (int32_t hg = h0; hg < std::min((x + 1) * per_slice, h0 + hc); ++hg)
+              for (size_t i = t; i < u; ++i) fn(int32_t(i), hg);
+          }
+      }
+  };
+  size_t i = 0;
+  for_each_item([&](int32_t t, int32_t) { cost[i++] = 2 + (p->wide_tiles[t].n_keys + kWideStageKeys - 1) / kWideStageKeys; });
+  static const int32_t even[1] = {1000};
+  hand_out(cost, p->n_wg, even, 1, owner, p->wg_begin);
+  p->wide_items.resize(n_items);
+  std::vector<int32_t> at(p->wg_begin.begin(), p->wg_begin.end() - 1);
+  i = 0;
+  for_each_item([&](int32_t t, int32_t hg) {
+    const int32_t head0 = hg * p->heads_per_wg;
+    p->wide_items[at[owner[i++]]++] = {t, head0 | (head0 / G) << 16};
+  });
+}
+
 // Validation, row groups, work list and decode tables of a plan (host only).
 sp_status build_plan(sp_ctx *ctx, const sp_segtable *t, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
                      sp_dtype dtype, sp_plan *p) {
@@ -367,7 +531,7 @@ sp_status build_plan(sp_ctx *ctx, const sp_segtable *t, int32_t n_q_heads, int32
   if (t->alibi_slopes) p->slopes.assign(t->alibi_slopes, t->alibi_slopes + n_q_heads);
 
   // --- row groups: fuse a child that is packed right behind its parent into the parent's run
-  std::vector<int32_t> group_of(S, -1), group_last;
+  std::vector<int32_t> group_of(S, -1), group_last, group_parent;   // group_parent: the segment that a group forks behind
   auto is_cached = [&](int32_t s) { return t->seg_cached && t->seg_cached[s] != 0; };
   // per row group: the row intervals [begin, end) that are computed (rows of cached segments are not)
   std::vector<std::vector<std::pair<int32_t, int32_t>>> live_rows;
@@ -411,6 +575,7 @@ sp_status build_plan(sp_ctx *ctx, const sp_segtable *t, int32_t n_q_heads, int32
       group_of[s] = static_cast<int32_t>(p->groups.size());
       group_last.push_back(s);
       p->groups.push_back(rg);
+      group_parent.push_back(par);
       live_rows.emplace_back();
       if (!is_cached(s)) add_live(group_of[s], 0, rg.len);
     }
@@ -480,7 +645,10 @@ sp_status build_plan(sp_ctx *ctx, const sp_segtable *t, int32_t n_q_heads, int32
     else if (n_items[1] <= most) p->tile_rows = 32;
   }
   const int32_t n_hg = n_q_heads / p->heads_per_wg;
-  {
+  wide_tiles(p, live_rows, group_parent, n_hg, n_cu);
+  if (p->wide) {
+    wide_work_list(p, n_hg, G, n_cu);
+  } else {
     std::vector<Tile> all_tiles;
     std::vector<int32_t> prompt_tile_off(B + 1, 0);
     size_t g = 0;
@@ -648,6 +816,8 @@ sp_status upload_plan(sp_ctx *ctx, sp_plan *p, void *reuse_blob, size_t reuse_by
   };
   const size_t o_ranges = add(p->ranges.data(), p->ranges.size() * sizeof(sp::KeyRange)),
                o_items = add(p->items.data(), p->items.size() * sizeof(sp::WorkItem)),
+               o_wt = add(p->wide_tiles.data(), p->wide_tiles.size() * sizeof(sp::WideTile)),
+               o_wi = add(p->wide_items.data(), p->wide_items.size() * sizeof(sp::WideItem)),
                o_wgb = add(p->wg_begin.data(), p->wg_begin.size() * 4),
                o_pos = add(p->pos.data(), p->pos.size() * 4), o_slopes = add(p->slopes.data(), p->slopes.size() * 4),
                o_poff = add(p->path_off.data(), p->path_off.size() * 4),
@@ -721,6 +891,8 @@ sp_status upload_plan(sp_ctx *ctx, sp_plan *p, void *reuse_blob, size_t reuse_by
   d = sp::PlanDev{};
   d.ranges = reinterpret_cast<const sp::KeyRange *>(base + o_ranges);
   d.items = reinterpret_cast<const sp::WorkItem *>(base + o_items);
+  d.wide_tiles = reinterpret_cast<const sp::WideTile *>(base + o_wt);
+  d.wide_items = reinterpret_cast<const sp::WideItem *>(base + o_wi);
   d.wg_begin = reinterpret_cast<const int32_t *>(base + o_wgb);
   d.tok_pos = p->pos.empty() ? nullptr : reinterpret_cast<const float *>(base + o_pos);
   d.slopes = p->slopes.empty() ? nullptr : reinterpret_cast<const float *>(base + o_slopes);
@@ -825,16 +997,41 @@ extern "C" sp_status sp_plan_info(const sp_plan *p, int64_t info[8]) {
   if (!p || !info) return fail(nullptr, SP_ERR_INVALID_ARG, "NULL argument");
   info[0] = p->n_prompts; info[1] = p->n_segments; info[2] = p->n_tokens; info[3] = p->n_slots;
   info[4] = int64_t(p->groups.size()); info[5] = p->n_tiles;
-  info[6] = int64_t(p->items.size());
+  info[6] = sp_plan_work_items(p, nullptr, 0, nullptr, 0);
   info[7] = p->max_ranges;
   return SP_OK;
+}
+
+// The wide kernel's work list in the form of the other: an item per row group of each tile.
+static void work_items_of_wide(const sp_plan *p, std::vector<sp::WorkItem> &items, std::vector<int32_t> &begin) {
+  begin.assign(1, 0);
+  for (int32_t s = 0; s < p->n_wg; ++s) {
+    for (int32_t i = p->wg_begin[s]; i < p->wg_begin[s + 1]; ++i) {
+      const sp::WideTile &t = p->wide_tiles[p->wide_items[i].tile];
+      int32_t prev = -1;
+      for (const sp::WideBlock &b : t.block) {
+        if (!b.n_rows) continue;
+        const int32_t g = p->tok_group[b.tok];
+        const sp::RowGroup &rg = p->groups[g];
+        if (g != prev)
+          items.push_back({rg.tok_start, b.tok - rg.tok_start, 0, rg.anc_keys, rg.range_off, rg.n_ranges, p->wide_items[i].heads,
+                           rg.n_ranges > 0 ? p->ranges[rg.range_off].tok_start : 0});
+        items.back().n_rows += b.n_rows;
+        prev = g;
+      }
+    }
+    begin.push_back(int32_t(items.size()));
+  }
 }
 
 extern "C" int64_t sp_plan_work_items(const sp_plan *p, int32_t *items_out, int64_t cap_items, int32_t *slot_begin_out,
                                       int64_t cap_slots) {
   if (!p || (cap_items > 0 && !items_out) || (cap_slots > 0 && !slot_begin_out)) return SP_ERR_INVALID_ARG;
-  const std::vector<sp::WorkItem> &it = p->items;
-  const std::vector<int32_t> &sb = p->wg_begin;
+  std::vector<sp::WorkItem> wide;
+  std::vector<int32_t> wide_begin;
+  if (p->wide) work_items_of_wide(p, wide, wide_begin);
+  const std::vector<sp::WorkItem> &it = p->wide ? wide : p->items;
+  const std::vector<int32_t> &sb = p->wide ? wide_begin : p->wg_begin;
   static_assert(sizeof(sp::WorkItem) == 8 * sizeof(int32_t), "an item is 8 int32");
   const int64_t n = std::min<int64_t>(cap_items, int64_t(it.size()));
   if (n > 0) std::memcpy(items_out, it.data(), size_t(n) * sizeof(sp::WorkItem));
@@ -931,8 +1128,9 @@ extern "C" sp_status sp_forkjoin_prefill(sp_ctx *ctx, const sp_plan *plan, const
     return fail(&ctx->err, SP_ERR_INVALID_ARG, "softmax_scale must be positive and finite");
   sp::PrefillArgs a{Q, K, V, O, q_tok_stride, q_head_stride, kv_tok_stride, kv_head_stride, softmax_scale};
   SP_HIP(ctx, hipSetDevice(ctx->device));
-  hipError_t e = plan->dtype == SP_BF16 ? sp::launch_prefill_bf16(plan, a, ctx->stream)
-                                        : sp::launch_prefill_f32(plan, a, ctx->stream);
+  hipError_t e = plan->dtype == SP_F32 ? sp::launch_prefill_f32(plan, a, ctx->stream)
+                 : plan->wide          ? sp::launch_prefill_wide(plan, a, ctx->stream)
+                                       : sp::launch_prefill_bf16(plan, a, ctx->stream);
   if (e != hipSuccess) return fail(&ctx->err, SP_ERR_HIP, "prefill launch: %s", hipGetErrorString(e));
   return SP_OK;
 }

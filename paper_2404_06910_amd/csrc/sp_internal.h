@@ -91,11 +91,43 @@ struct WorkItem {
   int32_t r0_start;    // first token of ancestor range 0 (the only one when n_ranges == 1)
 };
 
+// Work of the wide prefill kernel: tiles of kWideWaves blocks of up to 32 rows (over the query heads of a workgroup), and items
+// that name a tile and its heads.  The rows of a tile may belong to several row groups when these have the same ancestors; its
+// keys are one virtual sequence [ancestors ; own run of each group], cut into ranges.  With several groups every own run
+// begins at a multiple of 32 keys (a block of 32 never holds keys of two of them).
+constexpr int kWideWaves = 8, kWideStageKeys = 64, kWideRanges = 16;
+struct WideRange {
+  int32_t delta;       // virtual keys from the end of the range before up to `end` are the tokens min(delta + key, last)
+  int32_t end;         // the last range's has no end
+  int32_t last;
+  int32_t unused;
+};
+struct WideBlock {
+  int32_t tok;         // first row's token
+  int32_t n_rows;      // 0: none
+  int32_t first;       // first row's virtual key
+  int32_t base;        // first virtual key of its own run
+};
+struct WideTile {
+  int32_t n_keys;
+  int32_t anc;         // ancestor keys
+  int32_t anc_end;     // several groups: `anc` rounded up to 32; one group, whose own run follows directly: 0
+  int32_t unused;
+  WideBlock block[kWideWaves];
+  WideRange range[kWideRanges];
+};
+struct WideItem {
+  int32_t tile;
+  int32_t heads;       // first query head | KV head << 16
+};
+
 // Device-side view of a plan (plain pointers, passed by value to kernels).
 struct PlanDev {
   const KeyRange *ranges;
   const WorkItem *items;
   const int32_t *wg_begin;       // [n_wg + 1] slice of the (permuted) work list per workgroup slot
+  const WideTile *wide_tiles;
+  const WideItem *wide_items;
   const float *tok_pos;          // [n_tokens] or nullptr
   const float *slopes;           // [n_q_heads] or nullptr
   // decode tables
@@ -165,6 +197,9 @@ struct sp_plan {
   std::vector<sp::RowGroup> groups;
   std::vector<sp::KeyRange> ranges;
   std::vector<sp::WorkItem> items;
+  bool wide = false;                   // prefill by the wide kernel: its work list takes the place of `items`
+  std::vector<sp::WideTile> wide_tiles;
+  std::vector<sp::WideItem> wide_items;
   std::vector<int32_t> wg_begin;
   std::vector<int32_t> tok_group;      // token -> row group (host inspection)
   std::vector<int32_t> path_off, shared_rng_beg, shared_rng_end, path_rng_beg, path_rng_end;
@@ -198,6 +233,7 @@ struct PrefillArgs {
   float scale;
 };
 hipError_t launch_prefill_bf16(const sp_plan *plan, const PrefillArgs &a, hipStream_t s);
+hipError_t launch_prefill_wide(const sp_plan *plan, const PrefillArgs &a, hipStream_t s);
 hipError_t launch_prefill_f32(const sp_plan *plan, const PrefillArgs &a, hipStream_t s);
 
 hipError_t launch_saliency(const void *logits, sp_dtype dt, int64_t n_rows, int64_t vocab, int64_t row_stride,

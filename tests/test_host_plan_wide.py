@@ -1,0 +1,40 @@
+"""Plans that the wide bf16 prefill takes: that the rule takes them, and that their work covers every row and head once."""
+import numpy as np
+import pytest
+
+import sp_synth
+from paper_2404_06910_amd import binding as B
+
+from test_host_plan import _check_work_list
+from wide_plans import CASES, chain_table
+
+WIDE_SLOTS = 256                              # one workgroup per compute unit (the other kernel: 1024 or 512)
+
+
+def _slots(args, T, Hq, Hkv, d=128, dtype=B.SP_BF16, cached=None):
+    p = B.Plan(None, *args, T, Hq, Hkv, d, dtype, seg_cached=cached)
+    n = len(p.work_items()[1]) - 1
+    p.close()
+    return n
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_wide_work_list_covers_every_row_and_head_once(name):
+    Hq, Hkv, kw = CASES[name]
+    args, T, cached = chain_table(**kw)
+    assert _slots(args, T, Hq, Hkv, cached=cached) == WIDE_SLOTS
+    names = ("prompt_seg_off", "seg_tok_start", "seg_tok_len", "seg_parent", "seg_path")
+    _check_work_list(dict(zip(names, args), n_tokens=T), Hq, Hkv, cached=cached)
+
+
+def test_plans_that_stay_with_the_other_kernel():
+    args, T, _ = chain_table(prompts=8, chain=[600], docs=[128] * 12, query=24)
+    assert _slots(args, T, 32, 32, d=64) != WIDE_SLOTS
+    assert _slots(args, T, 32, 8) != WIDE_SLOTS                     # four heads per workgroup
+    args, T, _ = chain_table(prompts=1, chain=[600], docs=[128] * 12, query=24)
+    assert _slots(args, T, 32, 32) != WIDE_SLOTS                    # too little work
+    args, T, cached = chain_table(prompts=12, chain=[45] * 16, docs=[130] * 8, gap=1, cached_chain=True)
+    assert _slots(args, T, 32, 32, cached=cached) != WIDE_SLOTS     # more ranges than a tile has
+    wl = sp_synth.WORKLOADS["c2_mha7b_bf16"]
+    st = sp_synth.forkjoin_segtable(wl.preamble_len, [[wl.doc_len] * wl.n_paths] * wl.n_prompts, wl.query_len)
+    assert _slots((st.prompt_seg_off, st.seg_tok_start, st.seg_tok_len, st.seg_parent, st.seg_path), st.n_tokens, 32, 32) != WIDE_SLOTS

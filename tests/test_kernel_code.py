@@ -57,3 +57,8 @@ def test_decode_keeps_its_registers(kernels):
 def test_fp32_prefill_keeps_its_registers(kernels):
     for name, code in _named(kernels, "prefill_f32").items():
         assert not [c for c in code if c.startswith(("scratch_", "flat_load"))], name
+
+
+def test_wide_prefill_keeps_its_registers(kernels):
+    for name, code in _named(kernels, "prefill_wide").items():
+        assert not [c for c in code if c.startswith(("scratch_", "flat_"))], name
