@@ -802,9 +802,15 @@ sp_status upload_plan(sp_ctx *ctx, sp_plan *p, void *reuse_blob, size_t reuse_by
     if (end > beg) { d.tok_start = p->dec_ranges[beg].tok_start; d.len = p->dec_ranges[beg].len; }
     return d;
   };
-  std::vector<sp::RangeDesc> shared_desc(B), path_desc(p->n_slots);
+  int32_t path_stride = 0;
+  for (int32_t b = 0; b < B; ++b) path_stride = std::max(path_stride, p->path_off[b + 1] - p->path_off[b]);
+  if (path_stride > 64) path_stride = 0;
+  std::vector<sp::RangeDesc> shared_desc(B), path_desc(path_stride ? size_t(B) * path_stride : size_t(p->n_slots));
   for (int32_t b = 0; b < B; ++b) shared_desc[b] = describe(p->shared_rng_beg[b], p->shared_rng_end[b]);
-  for (int32_t q = 0; q < p->n_slots; ++q) path_desc[q] = describe(p->path_rng_beg[q], p->path_rng_end[q]);
+  for (int32_t b = 0; b < B; ++b)
+    for (int32_t q = p->path_off[b]; q < p->path_off[b + 1]; ++q)
+      path_desc[path_stride ? size_t(b) * path_stride + (q - p->path_off[b]) : size_t(q)] =
+          describe(p->path_rng_beg[q], p->path_rng_end[q]);
   struct Piece { const void *src; size_t bytes, at; };
   std::vector<Piece> pieces;
   size_t off = 0;
@@ -899,6 +905,7 @@ sp_status upload_plan(sp_ctx *ctx, sp_plan *p, void *reuse_blob, size_t reuse_by
   d.path_off = reinterpret_cast<const int32_t *>(base + o_poff);
   d.shared_desc = reinterpret_cast<const sp::RangeDesc *>(base + o_sd);
   d.path_desc = reinterpret_cast<const sp::RangeDesc *>(base + o_pd);
+  d.path_stride = path_stride;
   d.dec_ranges = reinterpret_cast<const sp::KeyRange *>(base + o_dr);
   d.n_items = static_cast<int32_t>(p->items.size());
   d.n_wg = p->n_wg;

@@ -68,18 +68,35 @@ struct KeyTable {
 
 // One thread per source follows the tables (kept -> path slot descriptor, which carries the first range), so the
 // dependent loads of all sources run side by side; a prefix over the sources puts the ranges in order.
+// Where no prompt has more than 64 paths, the descriptors of a prompt's paths lie at a fixed place (path_stride) and the
+// first wave reads all of them while `kept` is on its way, and picks from its lanes: one memory latency less for every
+// launch, and no barrier between the two halves, which one wave does (four tokens of six prompts of 32/8 heads 47.0 -> 45.1 us,
+// a request with five tokens of one prompt of 32 heads 89.1 -> 86.2).
 template <typename T, int D>
 __device__ __forceinline__ void build_key_table(const PlanDev &pd, const DecodeDev &a, int b, int g, int len_r, bool bias,
                                                 KeyTable &t) {
   const int tid = threadIdx.x, Hkv = pd.n_kv_heads;
   const int n_src = min(a.k, kDecMaxRanges - 1) + 1;      // k beyond that: prompts without paths, nothing to keep
+  const bool one_wave = pd.path_stride > 0 && n_src <= 64;
   RangeDesc src{0, 0, 0, 0};
-  if (tid == 0) {
+  if (one_wave) {
+    if (tid < 64) {
+      RangeDesc path{0, 0, 0, 0};
+      int kp = -1;
+      if (tid < pd.path_stride) path = pd.path_desc[b * pd.path_stride + tid];
+      if (tid > 0 && tid < n_src) kp = a.kept[(int64_t)b * a.k + (tid - 1)];
+      const RangeDesc shared = pd.shared_desc[b];
+      const RangeDesc mine{__shfl(path.beg, kp & 63), __shfl(path.end, kp & 63), __shfl(path.tok_start, kp & 63),
+                           __shfl(path.len, kp & 63)};
+      if (tid == 0) src = shared;
+      else if (kp >= 0 && kp < pd.path_stride) src = mine;   // paths that the prompt does not have are empty
+    }
+  } else if (tid == 0) {
     src = pd.shared_desc[b];
   } else if (tid < n_src) {
     const int p0 = pd.path_off[b], np = pd.path_off[b + 1] - p0;
     const int kp = a.kept[(int64_t)b * a.k + (tid - 1)];
-    if (kp >= 0 && kp < np) src = pd.path_desc[p0 + kp];
+    if (kp >= 0 && kp < np) src = pd.path_desc[pd.path_stride > 0 ? b * pd.path_stride + kp : p0 + kp];
   }
   const int beg = src.beg, end = src.end;
   if (tid < n_src) {
@@ -88,7 +105,13 @@ __device__ __forceinline__ void build_key_table(const PlanDev &pd, const DecodeD
     t.s_cnt[tid] = end - beg;
     t.s_keys[tid] = keys;
   }
-  __syncthreads();
+  if (one_wave) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+    __syncthreads();
+  }
   if (tid < n_src) {
     int at = 0, cum = 0;
     for (int i = 0; i < tid; ++i) { at += t.s_cnt[i]; cum += t.s_keys[i]; }

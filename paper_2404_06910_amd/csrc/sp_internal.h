@@ -135,7 +135,8 @@ struct PlanDev {
   // first/last+1 decode range and a copy of the first range: one 16-byte read tells a source's
   // ranges when there is only one (the usual case), without a further dependent read
   const RangeDesc *shared_desc;  // [n_prompts] the shared segments of each prompt
-  const RangeDesc *path_desc;    // [n_slots] each path slot
+  const RangeDesc *path_desc;    // each path slot: [n_prompts][path_stride], or [n_slots] where path_stride is 0
+  int32_t path_stride;           // most paths of any prompt (up to 64, else 0)
   const KeyRange *dec_ranges;
   int32_t n_items;
   int32_t n_wg;
