@@ -165,11 +165,13 @@ __device__ __forceinline__ int32_t clamp_slot(int32_t slot, int32_t n_slots) {
 }
 
 constexpr int kRedThreads = 256;
+constexpr int64_t kScanWideRows = 9 * 256, kScanWideSlots = 256;   // a scan of 1024 threads, see the launch
 constexpr int64_t kScanReads = int64_t(1) << 22, kScanRows = 4096, kScanRowsManySlots = 7168, kManySlots = 500;
 // One workgroup per slot.  Bound by the latency of two dependent reads (row_path, then the slot's rows); there is no atomic,
 // and the reads of row_path are independent of each other and come from the L2.  340 rows of 20 slots: 3.8 us (the atomic
-// kernel 6.2), 3840 rows of 160 slots: 4.7 us (6.1).
-__global__ __launch_bounds__(kRedThreads) void saliency_scan_kernel(const RowPart *__restrict__ part, int n_pieces,
+// kernel 6.2), 3840 rows of 160 slots: 4.7 us (6.1) with 256 threads.  NT: a thread has eight reads in flight, see the launch.
+template <int NT>
+__global__ __launch_bounds__(NT) void saliency_scan_kernel(const RowPart *__restrict__ part, int n_pieces,
                                                                     const int32_t *__restrict__ row_path, int32_t n_rows,
                                                                     const float *__restrict__ prior, int32_t n_slots,
                                                                     int mode, float *__restrict__ score) {
@@ -177,17 +179,17 @@ __global__ __launch_bounds__(kRedThreads) void saliency_scan_kernel(const RowPar
   const int32_t mine = blockIdx.x;
   long long q = 0;
   uint32_t count = 0, flags = 0;
-  for (int32_t r0 = threadIdx.x; r0 < n_rows; r0 += U * kRedThreads) {
+  for (int32_t r0 = threadIdx.x; r0 < n_rows; r0 += U * NT) {
     int32_t slot[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int32_t r = r0 + u * kRedThreads;
+      const int32_t r = r0 + u * NT;
       slot[u] = r < n_rows ? clamp_slot(row_path[r], n_slots) : -1;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (slot[u] == mine) {
-        const RowLp v = row_lp(part, r0 + u * kRedThreads, n_pieces);
+        const RowLp v = row_lp(part, r0 + u * NT, n_pieces);
         q += v.q;
         count += v.scored;
         flags |= v.flags;
@@ -199,14 +201,14 @@ __global__ __launch_bounds__(kRedThreads) void saliency_scan_kernel(const RowPar
     count += __shfl_xor(count, off);
     flags |= __shfl_xor(flags, off);
   }
-  __shared__ long long s_q[kRedThreads / 64];
-  __shared__ uint32_t s_c[kRedThreads / 64], s_f[kRedThreads / 64];
+  __shared__ long long s_q[NT / 64];
+  __shared__ uint32_t s_c[NT / 64], s_f[NT / 64];
   const int wave = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) { s_q[wave] = q; s_c[wave] = count; s_f[wave] = flags; }
   __syncthreads();
   if (threadIdx.x != 0) return;
 #pragma unroll
-  for (int w = 1; w < kRedThreads / 64; ++w) { q += s_q[w]; count += s_c[w]; flags |= s_f[w]; }
+  for (int w = 1; w < NT / 64; ++w) { q += s_q[w]; count += s_c[w]; flags |= s_f[w]; }
   score[mine] = slot_score(q, count, flags, mode, prior, mine);
 }
 
@@ -325,8 +327,18 @@ hipError_t launch_saliency(const void *logits, sp_dtype dt, int64_t n_rows, int6
   // slots as well (a launch ends at 2^24 workgroups).
   if (n_rows <= (n_slots >= kManySlots ? kScanRowsManySlots : kScanRows) &&
       std::max<int64_t>(n_rows, 1) * n_slots <= kScanReads) {
-    hipLaunchKernelGGL(saliency_scan_kernel, dim3(unsigned(n_slots)), dim3(kRedThreads), 0, s, part, n_pieces, row_path,
-                       int32_t(n_rows), prior, n_slots, mode, score);
+    // A thread has eight reads of row_path in flight.  With 256 threads more rows than 2048 take a second round of them, each
+    // a memory latency, and 1024 threads one; but a workgroup of 1024 leaves room for one other on a compute unit, so many
+    // slots wait for places.  us a call of 512 bf16 logits a row, 256 / 1024 threads: 2049 rows of 20 slots 8.0 / 8.3, 2500 of
+    // 160 8.7 / 8.45, 3000 of 20 9.2 / 8.6, 4096 of 100 10.3 / 9.5, 4096 of 500 10.6 / 10.65, 4096 of 1000 11.2 / 13.4, 3000 of
+    // 1300 10.3 / 14.7; 3840 rows of 50432 logits and 160 slots 62.7 / 61.7, with top-k 67.1 / 65.9.
+    auto scan = [&](auto threads) {
+      constexpr int NT = decltype(threads)::value;
+      hipLaunchKernelGGL(saliency_scan_kernel<NT>, dim3(unsigned(n_slots)), dim3(NT), 0, s, part, n_pieces, row_path,
+                         int32_t(n_rows), prior, n_slots, mode, score);
+    };
+    if (n_rows > kScanWideRows && n_slots <= kScanWideSlots) scan(std::integral_constant<int, 1024>{});
+    else scan(std::integral_constant<int, 256>{});
     return hipGetLastError();
   }
   const unsigned grid = n_rows > 0 ? unsigned((n_rows + kRedThreads - 1) / kRedThreads) : 1u;
