@@ -53,6 +53,7 @@ struct DecodeDev {
   float *part;             // with one workgroup per piece: [row][piece][D] sums, then [row][piece] {max, sum}
   uint32_t *count;         // and one arrival counter per (prompt, KV head, chunk of query heads), zero between launches
   int32_t chunks_together; // see my_share
+  int32_t few_wgs;         // see build_key_table
 };
 
 // The key list of one (prompt, KV head) as ranges with running key counts, in LDS: the prefill ranges of the
@@ -71,13 +72,14 @@ struct KeyTable {
 // Where no prompt has more than 64 paths, the descriptors of a prompt's paths lie at a fixed place (path_stride) and the
 // first wave reads all of them while `kept` is on its way, and picks from its lanes: one memory latency less for every
 // launch, and no barrier between the two halves, which one wave does (four tokens of six prompts of 32/8 heads 47.0 -> 45.1 us,
-// a request with five tokens of one prompt of 32 heads 89.1 -> 86.2).
+// a request with five tokens of one prompt of 32 heads 89.1 -> 86.2).  With more than four workgroups to a compute unit the
+// others' streams hide the latency, and the reads of paths that are not kept cost 0.2 % (64 prompts, 32 heads: 91.1 / 91.4).
 template <typename T, int D>
 __device__ __forceinline__ void build_key_table(const PlanDev &pd, const DecodeDev &a, int b, int g, int len_r, bool bias,
                                                 KeyTable &t) {
   const int tid = threadIdx.x, Hkv = pd.n_kv_heads;
   const int n_src = min(a.k, kDecMaxRanges - 1) + 1;      // k beyond that: prompts without paths, nothing to keep
-  const bool one_wave = pd.path_stride > 0 && n_src <= 64;
+  const bool one_wave = a.few_wgs && pd.path_stride > 0 && n_src <= 64;
   RangeDesc src{0, 0, 0, 0};
   if (one_wave) {
     if (tid < 64) {
@@ -750,6 +752,7 @@ static hipError_t launch_decode_t(const sp_plan *plan, DecodeDev &d, const Decod
   }
   d.chunks_together = ny > 1 && base % 8 == 0 && base / 8 <= 65535;
   const unsigned n_z = unsigned(d.n_pieces / d.pieces_per_wg);
+  d.few_wgs = int64_t(base) * ny * n_z <= int64_t(4) * plan->ctx->n_cu;
   const dim3 grid = d.chunks_together ? dim3(8u * unsigned(ny), n_z, unsigned(base) / 8) : dim3(unsigned(base), n_z, unsigned(ny));
   const dim3 block(kDecThreads);
   auto launch_as = [&](auto heads, auto bias, auto stream) {
@@ -776,7 +779,7 @@ static hipError_t launch_decode_t(const sp_plan *plan, DecodeDev &d, const Decod
 
 hipError_t launch_decode(const sp_plan *plan, const DecodeArgs &a, hipStream_t s) {
   DecodeDev d{a.kept, a.k, a.Kp, a.Vp, a.kv_tok_stride, a.kv_head_stride, a.Kr, a.Vr, a.pos_resp, a.resp_capacity,
-              a.resp_len, a.resp_len_add, a.new_pos, a.q_new, a.k_new, a.v_new, a.o_out, a.scale, 1, 1, nullptr, nullptr, 0};
+              a.resp_len, a.resp_len_add, a.new_pos, a.q_new, a.k_new, a.v_new, a.o_out, a.scale, 1, 1, nullptr, nullptr, 0, 0};
   if (plan->dtype == SP_BF16)
     return plan->head_dim == 128 ? launch_decode_t<__bf16, 128>(plan, d, a, s) : launch_decode_t<__bf16, 64>(plan, d, a, s);
   return plan->head_dim == 128 ? launch_decode_t<float, 128>(plan, d, a, s) : launch_decode_t<float, 64>(plan, d, a, s);
