@@ -552,11 +552,11 @@ def _bench_iterative_round(ctx, torch, B, wl, sets, scale, chain=(3, 7, 11, 15),
     off, start, length, parent, path, cached, n_tok = tabs[0]
     rows = int(sum(int(l) for l, c in zip(length, cached) if not c))
     by = n_tok * kv_bytes_per_token(wl.n_kv_heads, wl.head_dim, 2) + rows * 2 * wl.n_q_heads * wl.head_dim * 2
-    return dict(tm, kernel="prefill_bf16_kernel", rows="documents not yet kept and their query copies",
+    return dict(tm, kernel="prefill_wide_kernel", rows="documents not yet kept and their query copies",
                 chain_documents=len(chain), algorithmic_flops=flops, tflops=round(flops / (ms * 1e-3) / 1e12, 2),
                 algorithmic_bytes=by, hbm_frac=round(by / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                 mfma_frac=round(flops / (ms * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS, 4),
-                traffic=_stored_traffic("prefill_bf16_kernel:" + wl.name + ":iterative_round"),
+                traffic=_stored_traffic("prefill_wide_kernel:" + wl.name + ":iterative_round"),
                 traffic_source="stored: profiles/traffic.json",
                 plan_update_ms=round(float(np.median(ts[2:])) * 1e3, 3))
 

@@ -357,6 +357,10 @@ void hand_out(const std::vector<int32_t> &cost, int32_t n_slots, const int32_t *
 // stages a unit, 51 against 52 us; 24 + 8 behind 768, 7.5 stages, 35 against 35).  Of the plans that the rule lets in it was
 // 1.07 to 1.30 times as fast (24 + 8 tokens behind 768: 149 -> 114 us; 220 + 24 behind 1400: 930 -> 829).  Four heads per
 // workgroup share their K/V rows in the other kernel already: 0.85 to 1.05 times as fast here, so they stay there.
+// The fit holds for tiles whose waves compute on most stages (three quarters and more in those plans).  A tile of eight short
+// query copies behind their own cached documents streams eight documents for all and computes on a sixth: 24 rows behind 64 +
+// 128 keys 104 us with the other kernel and 108 here, behind 64 + 64 to 220 110 and 118, behind 300 + 128 (a third) 129 and 128.
+// So at least half of the stages have to be computed on.
 void wide_tiles(sp_plan *p, const std::vector<std::vector<std::pair<int32_t, int32_t>>> &live_rows,
                 const std::vector<int32_t> &group_parent, int32_t n_hg, int n_cu) {
   using namespace sp;
@@ -457,7 +461,8 @@ void wide_tiles(sp_plan *p, const std::vector<std::vector<std::pair<int32_t, int
   const bool pair = p->heads_per_wg == 2;
   const double narrow = 0.25 * (pair ? 1.32 * narrow_stages + 7.7 * narrow_items : 1.23 * narrow_stages + 5.5 * narrow_items),
                wide = pair ? 4.2 / 8 * steps + 9.3 * n_tiles : 2.0 / 8 * steps + 8.8 * n_tiles;
-  if (stages * n_hg < int64_t(40) * n_cu || 0.97 * wide > narrow) return;
+  const bool mostly_computed = 2 * steps >= stages * NB;
+  if (stages * n_hg < int64_t(40) * n_cu || !mostly_computed || 0.97 * wide > narrow) return;
   p->wide = true;
   p->wide_tiles.reserve(size_t(n_tiles));
   for_each_tile(emit);

@@ -323,7 +323,7 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_bf16_kernel(PlanDev pd, co
       } else {
         // Blocks of 32 keys; those entirely above this wave's diagonal are not computed.  At 128 dims the block is a function
         // that is optimised by itself before it becomes part of the loop: that takes fewer registers, which there decides
-        // between spilling and not (iterative round of 32 heads 376 -> 367 us).  At 64 dims, where there are enough, its
+        // between spilling and not (iterative round of 32 heads, which has a kernel of its own since, 376 -> 367 us).  At 64 dims, where there are enough, its
         // schedule is the worse one (iterative round of 32/8 heads with bias, ragged: 219.7 us in place, 234.8 as a function).
         if constexpr (D == 128) {
           auto block = [&](const int sub) {

@@ -38,3 +38,8 @@ def test_plans_that_stay_with_the_other_kernel():
     wl = sp_synth.WORKLOADS["c2_mha7b_bf16"]
     st = sp_synth.forkjoin_segtable(wl.preamble_len, [[wl.doc_len] * wl.n_paths] * wl.n_prompts, wl.query_len)
     assert _slots((st.prompt_seg_off, st.seg_tok_start, st.seg_tok_len, st.seg_parent, st.seg_path), st.n_tokens, 32, 32) != WIDE_SLOTS
+    # query copies behind cached documents: a wave would compute on few of its tile's stages
+    args, T, _ = chain_table(prompts=8, chain=[64], docs=[128] * 20, query=24)
+    cached = np.ones(len(args[1]), np.uint8)
+    cached[np.flatnonzero(args[2] == 24)] = 0
+    assert _slots(args, T, 32, 32, cached=cached) != WIDE_SLOTS
