@@ -131,7 +131,8 @@ sp_status sp_plan_info(const sp_plan *plan, int64_t info[8]);
  * index of its first ancestor range, number of ancestor ranges, first query head | KV head << 16, first
  * token of ancestor range 0}; the rows see the ancestor ranges (sp_plan_key_ranges: pairs {first token,
  * length}, root to leaf) completely and the rows of their own group causally.  A kernel whose tiles hold rows
- * of several groups lists an item per group of each tile.  Worker slot s (a wave or a
+ * of several groups, or rows of a group before and behind a cached segment, lists an item per run of consecutive
+ * rows of each tile.  Worker slot s (a wave or a
  * workgroup, depending on the kernel the plan selected; sp_plan_work_slots of them) owns items
  * [slot_begin[s], slot_begin[s+1]).  Each call writes at most cap entries and returns the full count, or a
  * negative sp_status (slot_begin has sp_plan_work_slots() + 1 entries).  HOST pointers. */

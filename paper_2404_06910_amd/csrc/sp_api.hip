@@ -1014,37 +1014,52 @@ extern "C" sp_status sp_plan_info(const sp_plan *p, int64_t info[8]) {
   return SP_OK;
 }
 
-// The wide kernel's work list in the form of the other: an item per row group of each tile.
-static void work_items_of_wide(const sp_plan *p, std::vector<sp::WorkItem> &items, std::vector<int32_t> &begin) {
-  begin.assign(1, 0);
+// The wide kernel's work list in the form of the other: an item per run of consecutive rows of one group in each tile (a tile
+// may hold rows of several groups, and of a group rows before and behind a cached segment).  fn(item) for each; slot(n) with
+// the items so far before each slot and behind the last.
+template <class Fn, class Slot>
+static void for_each_wide_item(const sp_plan *p, Fn &&fn, Slot &&slot) {
+  int64_t n = 0;
+  slot(n);
   for (int32_t s = 0; s < p->n_wg; ++s) {
     for (int32_t i = p->wg_begin[s]; i < p->wg_begin[s + 1]; ++i) {
-      const sp::WideTile &t = p->wide_tiles[p->wide_items[i].tile];
-      int32_t prev = -1;
-      for (const sp::WideBlock &b : t.block) {
-        if (!b.n_rows) continue;
-        const int32_t g = p->tok_group[b.tok];
+      const sp::WideItem &wi = p->wide_items[i];
+      const sp::WideTile &t = p->wide_tiles[wi.tile];
+      for (int32_t b = 0; b < sp::kWideWaves && t.block[b].n_rows;) {
+        const int32_t tok = t.block[b].tok, g = p->tok_group[tok];
         const sp::RowGroup &rg = p->groups[g];
-        if (g != prev)
-          items.push_back({rg.tok_start, b.tok - rg.tok_start, 0, rg.anc_keys, rg.range_off, rg.n_ranges, p->wide_items[i].heads,
-                           rg.n_ranges > 0 ? p->ranges[rg.range_off].tok_start : 0});
-        items.back().n_rows += b.n_rows;
-        prev = g;
+        int32_t rows = 0;
+        for (; b < sp::kWideWaves && t.block[b].n_rows && t.block[b].tok == tok + rows && p->tok_group[tok + rows] == g; ++b)
+          rows += t.block[b].n_rows;
+        fn(sp::WorkItem{rg.tok_start, tok - rg.tok_start, rows, rg.anc_keys, rg.range_off, rg.n_ranges, wi.heads,
+                        rg.n_ranges > 0 ? p->ranges[rg.range_off].tok_start : 0});
+        ++n;
       }
     }
-    begin.push_back(int32_t(items.size()));
+    slot(n);
   }
 }
 
 extern "C" int64_t sp_plan_work_items(const sp_plan *p, int32_t *items_out, int64_t cap_items, int32_t *slot_begin_out,
                                       int64_t cap_slots) {
   if (!p || (cap_items > 0 && !items_out) || (cap_slots > 0 && !slot_begin_out)) return SP_ERR_INVALID_ARG;
-  std::vector<sp::WorkItem> wide;
-  std::vector<int32_t> wide_begin;
-  if (p->wide) work_items_of_wide(p, wide, wide_begin);
-  const std::vector<sp::WorkItem> &it = p->wide ? wide : p->items;
-  const std::vector<int32_t> &sb = p->wide ? wide_begin : p->wg_begin;
   static_assert(sizeof(sp::WorkItem) == 8 * sizeof(int32_t), "an item is 8 int32");
+  if (p->wide) {
+    int64_t n = 0, slots = 0;
+    for_each_wide_item(
+        p,
+        [&](const sp::WorkItem &w) {
+          if (n < cap_items) std::memcpy(items_out + 8 * n, &w, sizeof w);
+          ++n;
+        },
+        [&](int64_t so_far) {
+          if (slots < cap_slots) slot_begin_out[slots] = int32_t(so_far);
+          ++slots;
+        });
+    return n;
+  }
+  const std::vector<sp::WorkItem> &it = p->items;
+  const std::vector<int32_t> &sb = p->wg_begin;
   const int64_t n = std::min<int64_t>(cap_items, int64_t(it.size()));
   if (n > 0) std::memcpy(items_out, it.data(), size_t(n) * sizeof(sp::WorkItem));
   for (int64_t i = 0; i < cap_slots && i < int64_t(sb.size()); ++i) slot_begin_out[i] = sb[i];
