@@ -128,8 +128,8 @@ sp_status sp_plan_update(sp_plan *plan, const sp_segtable *table);
 sp_status sp_plan_info(const sp_plan *plan, int64_t info[8]);
 /* Host inspection of the prefill work list as the kernel walks it.  Item i is 8 int32:
  * {first token of its row group, first row of the tile inside the group, rows in the tile, ancestor keys,
- * index of its first ancestor range, number of ancestor ranges, first query head | KV head << 16, first
- * token of ancestor range 0}; the rows see the ancestor ranges (sp_plan_key_ranges: pairs {first token,
+ * index of its first ancestor range, number of ancestor ranges, first query head | KV head << 16 (16 bits
+ * each, unsigned), first token of ancestor range 0}; the rows see the ancestor ranges (sp_plan_key_ranges: pairs {first token,
  * length}, root to leaf) completely and the rows of their own group causally.  A kernel whose tiles hold rows
  * of several groups, or rows of a group before and behind a cached segment, lists an item per run of consecutive
  * rows of each tile.  Worker slot s (a wave or a

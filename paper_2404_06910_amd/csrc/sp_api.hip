@@ -505,7 +505,7 @@ void wide_work_list(sp_plan *p, int32_t n_hg, int32_t G, int n_cu) {
   i = 0;
   for_each_item([&](int32_t t, int32_t hg) {
     const int32_t head0 = hg * p->heads_per_wg;
-    p->wide_items[at[owner[i++]]++] = {t, head0 | (head0 / G) << 16};
+    p->wide_items[at[owner[i++]]++] = {t, sp::pack_heads(head0, head0 / G)};
   });
 }
 
@@ -619,7 +619,7 @@ sp_status build_plan(sp_ctx *ctx, const sp_segtable *t, int32_t n_q_heads, int32
     w.tok_start = rg.tok_start; w.row0 = tl.row0;
     w.n_rows = tl.n_rows;
     w.anc_keys = rg.anc_keys; w.range_off = rg.range_off; w.n_ranges = rg.n_ranges;
-    w.head0 = head0 | (kv_head << 16);
+    w.head0 = sp::pack_heads(head0, kv_head);
     w.r0_start = rg.n_ranges > 0 ? p->ranges[rg.range_off].tok_start : 0;
     return w;
   };

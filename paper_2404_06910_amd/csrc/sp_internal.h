@@ -78,6 +78,9 @@ struct RangeDesc {
   int32_t len;
 };
 
+// A query head and its KV head, 16 bits each: both unsigned (KV heads from 32768 on set the sign bit).
+inline int32_t pack_heads(int32_t head, int32_t kv_head) { return int32_t(uint32_t(head) | uint32_t(kv_head) << 16); }
+
 // One prefill work item: a tile of query rows of one row group, for one group of query heads.
 // Self-contained (one 32-byte scalar load), so a workgroup never chases pointers between items.
 struct WorkItem {
@@ -87,7 +90,7 @@ struct WorkItem {
   int32_t anc_keys;    // keys in the ancestor ranges
   int32_t range_off;   // first ancestor range
   int32_t n_ranges;
-  int32_t head0;       // first query head handled by the workgroup | its KV head << 16
+  int32_t head0;       // pack_heads(first query head handled by the workgroup, its KV head)
   int32_t r0_start;    // first token of ancestor range 0 (the only one when n_ranges == 1)
 };
 
@@ -118,7 +121,7 @@ struct WideTile {
 };
 struct WideItem {
   int32_t tile;
-  int32_t heads;       // first query head | KV head << 16
+  int32_t heads;       // pack_heads(first query head, its KV head)
 };
 
 // Device-side view of a plan (plain pointers, passed by value to kernels).

@@ -236,8 +236,8 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_bf16_kernel(PlanDev pd, co
     w.tok_start = __builtin_amdgcn_readfirstlane(a.x); w.row0 = __builtin_amdgcn_readfirstlane(a.y);
     w.n_rows = __builtin_amdgcn_readfirstlane(a.z); w.anc_keys = __builtin_amdgcn_readfirstlane(a.w);
     w.range_off = __builtin_amdgcn_readfirstlane(b.x); w.n_ranges = __builtin_amdgcn_readfirstlane(b.y);
-    const int heads = __builtin_amdgcn_readfirstlane(b.z);    // query head | KV head << 16
-    w.head0 = heads & 0xffff; w.kv_head = heads >> 16;
+    const uint32_t heads = __builtin_amdgcn_readfirstlane(b.z);    // query head | KV head << 16, 16 bits each
+    w.head0 = int(heads & 0xffff); w.kv_head = int(heads >> 16);
     w.r0_start = __builtin_amdgcn_readfirstlane(b.w);
     return w;
   };

@@ -74,8 +74,9 @@ __global__ __launch_bounds__(64, 2) void prefill_f32_kernel(PlanDev pd, const fl
   const int row_tok = w.tok_start + w.row0 + row;
   const int my_limit = w.anc_keys + w.row0 + row;            // last virtual key that this lane's row sees
   const int first_limit = w.anc_keys + w.row0 + r0, last_limit = first_limit + rows - 1;
-  const float *Kh = K + int64_t(w.head0 >> 16) * kv_hs + 4 * quad;
-  const float *Vg = V + int64_t(w.head0 >> 16) * kv_hs, *Vh = Vg + 4 * l16;
+  const int64_t kv_head = uint32_t(w.head0) >> 16;
+  const float *Kh = K + kv_head * kv_hs + 4 * quad;
+  const float *Vg = V + kv_head * kv_hs, *Vh = Vg + 4 * l16;
 
   // The key range that holds virtual key `base`: [base, base + len) are the tokens from tok on.  Range n_ranges is the
   // own run.  base, len and tok are the same for all lanes.

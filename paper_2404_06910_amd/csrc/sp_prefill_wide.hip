@@ -166,10 +166,11 @@ __global__ __launch_bounds__(64 * (NW + NP), 3) void prefill_wide_kernel(PlanDev
     if (tid < n_it) s_heads[tid] = pd.wide_items[x0 + batch + tid].heads;
     __syncthreads();
 
+    auto kv_of = [&](int li) { return int(uint32_t(__builtin_amdgcn_readfirstlane(s_heads[li])) >> 16); };
     auto stages_of = [&](int li) { return (__builtin_amdgcn_readfirstlane(s_tiles[li].n_keys) + BK - 1) / BK; };
     if (wave >= NW) {
       __builtin_amdgcn_s_setprio(3);
-      int li = 0, st = -NQ, ns = stages_of(0), kv = __builtin_amdgcn_readfirstlane(s_heads[0]) >> 16;
+      int li = 0, st = -NQ, ns = stages_of(0), kv = kv_of(0);
       int told = seq;                                      // stages that the computing waves know of
 #pragma unroll 1
       while (li < n_it) {
@@ -190,7 +191,7 @@ __global__ __launch_bounds__(64 * (NW + NP), 3) void prefill_wide_kernel(PlanDev
         }
         if (++st == ns) {
           st = -NQ;
-          if (++li < n_it) { ns = stages_of(li); kv = __builtin_amdgcn_readfirstlane(s_heads[li]) >> 16; }
+          if (++li < n_it) { ns = stages_of(li); kv = kv_of(li); }
         }
       }
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
