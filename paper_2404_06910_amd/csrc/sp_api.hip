@@ -354,13 +354,15 @@ void hand_out(const std::vector<int32_t> &cost, int32_t n_slots, const int32_t *
 //   wide          2.0 per stage that all eight waves compute on and 8.8 per tile;  two heads a workgroup 4.2 and 9.3
 // The wide kernel takes the plan where it comes out at 1/0.97 of the other's time or less, and only where every compute unit
 // has 40 stages or more: with fewer its few large tiles end unevenly (one prompt of 32 heads: 128 + 24 tokens behind 448, 17
-// stages a unit, 51 against 52 us; 24 + 8 behind 768, 7.5 stages, 35 against 35).  Of the plans that the rule lets in it was
+// stages a unit, 51 against 52 us; 24 + 8 behind 768, 7.5 stages, 35 against 35).  Of those 76 plans the ones let in were
 // 1.07 to 1.30 times as fast (24 + 8 tokens behind 768: 149 -> 114 us; 220 + 24 behind 1400: 930 -> 829).  Four heads per
 // workgroup share their K/V rows in the other kernel already: 0.85 to 1.05 times as fast here, so they stay there.
 // The fit holds for tiles whose waves compute on most stages (three quarters and more in those plans).  A tile of eight short
 // query copies behind their own cached documents streams eight documents for all and computes on a sixth: 24 rows behind 64 +
 // 128 keys 104 us with the other kernel and 108 here, behind 64 + 64 to 220 110 and 118, behind 300 + 128 (a third) 129 and 128.
 // So at least half of the stages have to be computed on.
+//
+// These are means over the compute units.  With few tiles to a unit the slowest unit decides, see wide_ends_first.
 void wide_tiles(sp_plan *p, const std::vector<std::vector<std::pair<int32_t, int32_t>>> &live_rows,
                 const std::vector<int32_t> &group_parent, int32_t n_hg, int n_cu) {
   using namespace sp;
@@ -371,9 +373,10 @@ void wide_tiles(sp_plan *p, const std::vector<std::vector<std::pair<int32_t, int
   auto one_group = [](const std::vector<Block> &bl) { return bl.front().group == bl.back().group; };
 
   // stages of a tile, and stages that each of its blocks is computed on, summed up
-  int64_t n_tiles = 0, stages = 0, steps = 0;
-  auto count = [&](const std::vector<Block> &bl) {
+  struct Size { int32_t stages, steps; };
+  auto size_of = [&](const std::vector<Block> &bl) -> Size {
     const bool one = one_group(bl);
+    int32_t steps = 0;
     const int32_t anc = p->groups[bl[0].group].anc_keys;
     int32_t at = one ? anc : pad(anc), keys = 0;
     const int32_t shared = one ? 0 : (at + kWideStageKeys - 1) / kWideStageKeys;
@@ -383,7 +386,13 @@ void wide_tiles(sp_plan *p, const std::vector<std::vector<std::pair<int32_t, int
       const int32_t last = (at + bl[i].row0 + bl[i].n_rows - 1) / kWideStageKeys;
       steps += shared + last - std::max(shared - 1, one ? -1 : at / kWideStageKeys - 1);
     }
-    stages += (at + keys + kWideStageKeys - 1) / kWideStageKeys;
+    return {(at + keys + kWideStageKeys - 1) / kWideStageKeys, steps};
+  };
+  int64_t n_tiles = 0, stages = 0, steps = 0;
+  auto count = [&](const std::vector<Block> &bl) {
+    const Size s = size_of(bl);
+    stages += s.stages;
+    steps += s.steps;
     ++n_tiles;
   };
   auto emit = [&](const std::vector<Block> &bl) {
@@ -392,6 +401,7 @@ void wide_tiles(sp_plan *p, const std::vector<std::vector<std::pair<int32_t, int
     const bool one = one_group(bl);
     t.anc = g0.anc_keys;
     t.anc_end = one ? 0 : pad(g0.anc_keys);
+    t.steps = size_of(bl).steps;
     int32_t n = 0, at = 0;
     for (int32_t r = 0; r < g0.n_ranges; ++r) {
       const KeyRange &kr = p->ranges[g0.range_off + r];
@@ -509,6 +519,51 @@ void wide_work_list(sp_plan *p, int32_t n_hg, int32_t G, int n_cu) {
   });
 }
 
+// Whether the wide kernel's slowest compute unit is done before the other's, by the lists that both would walk.
+//
+// Its tiles are few and large: a unit with one more than the others holds up the launch, and the means of wide_tiles do not see
+// it.  Of 4326 plans that wide_tiles lets in (1 to 8 prompts, 1 to 32 documents of 1 to 1000 tokens behind 500 to 32768, 8 to 40
+// heads, 0.1 to 60 tiles per unit) 289 were slower than with the other kernel by 3 % or more, down to 0.68 of its speed: 3
+// prompts of 3 documents of 128 + 24 tokens behind 4096, 32 heads, 1.12 tiles a unit, 152 us and 217; 5 of 6 documents of 40 + 8
+// behind 8192, 1.25 tiles, 350 and 443.  Times in us, as fitted to these plans and to those named above wide_tiles
+// (rms 4-7 % of either kernel's):
+//   wide          per tile 1.05 a stage + 0.85 a stage that all its waves compute on + 4.5
+//   other kernel  per workgroup 0.84 a stage + 3.4 an item with the unit to itself, and 1.18, 1.22 and 1.35 times that while
+//                 two, three and four share it
+// Of the plans that pass, none was slower by 3 % (0.971), and of 1560 others made the same way three (0.93 to 0.95); of some 700
+// that do not pass, 24 were faster with the wide kernel by 5 % or more (two 1.2 times, else up to 1.12).  From ten tiles a unit
+// on none of 252 was slower, and nothing is asked.  The second list takes 0.05 to 0.1 ms of the plan's making.
+constexpr int kWideFewTiles = 10;
+bool wide_ends_first(const sp_plan *p, const std::vector<int32_t> &item_stages, const std::vector<int32_t> &owner, int32_t n_slots,
+                     int32_t rounds) {
+  const double NB = sp::kWideWaves / p->heads_per_wg;
+  double wide = 0;
+  for (int32_t s = 0; s < p->n_wg; ++s) {
+    double t = 0;
+    for (int32_t i = p->wg_begin[s]; i < p->wg_begin[s + 1]; ++i) {
+      const sp::WideTile &w = p->wide_tiles[p->wide_items[i].tile];
+      t += 1.05 * ((w.n_keys + sp::kWideStageKeys - 1) / sp::kWideStageKeys) + 0.85 * w.steps / NB + 4.5;
+    }
+    wide = std::max(wide, t);
+  }
+  std::vector<double> load(n_slots, 0.0);
+  for (size_t i = 0; i < item_stages.size(); ++i) load[owner[i]] += 0.84 * item_stages[i] + 3.4;
+  // the slots of a unit: one per dispatch round, as in hand_out
+  static const double slowed[4] = {1.0, 1.18, 1.22, 1.35};
+  const int32_t per_xcd = n_slots / 8, units = std::max(1, per_xcd / rounds);
+  double other = 0, mine[4];
+  for (int32_t x = 0; x < 8; ++x)
+    for (int32_t u = 0; u < units; ++u) {
+      int32_t n = 0;
+      for (int32_t s = u; s < per_xcd && n < 4; s += units) mine[n++] = load[x * per_xcd + s];
+      std::sort(mine, mine + n);
+      double t = 0, done = 0;
+      for (int32_t i = 0; i < n; done = mine[i++]) t += (mine[i] - done) * slowed[n - 1 - i];
+      other = std::max(other, t);
+    }
+  return wide <= other;
+}
+
 // Validation, row groups, work list and decode tables of a plan (host only).
 sp_status build_plan(sp_ctx *ctx, const sp_segtable *t, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
                      sp_dtype dtype, sp_plan *p) {
@@ -611,7 +666,6 @@ sp_status build_plan(sp_ctx *ctx, const sp_segtable *t, int32_t n_q_heads, int32
         if (rem) tiles.push_back({int32_t(g), iv.first, rem});
         for (int32_t r = iv.first + rem; r < iv.second; r += tile_rows) tiles.push_back({int32_t(g), r, tile_rows});
       }
-    p->n_tiles += static_cast<int32_t>(tiles.size());
   };
   auto make_item = [&](const Tile &tl, int32_t head0, int32_t kv_head) {
     const sp::RowGroup &rg = p->groups[tl.group];
@@ -651,9 +705,9 @@ sp_status build_plan(sp_ctx *ctx, const sp_segtable *t, int32_t n_q_heads, int32
   }
   const int32_t n_hg = n_q_heads / p->heads_per_wg;
   wide_tiles(p, live_rows, group_parent, n_hg, n_cu);
-  if (p->wide) {
-    wide_work_list(p, n_hg, G, n_cu);
-  } else {
+  if (p->wide) wide_work_list(p, n_hg, G, n_cu);
+  const bool few_tiles = p->wide && int64_t(p->wide_items.size()) < int64_t(kWideFewTiles) * n_cu;
+  if (!p->wide || few_tiles) {
     std::vector<Tile> all_tiles;
     std::vector<int32_t> prompt_tile_off(B + 1, 0);
     size_t g = 0;
@@ -709,18 +763,30 @@ sp_status build_plan(sp_ctx *ctx, const sp_segtable *t, int32_t n_q_heads, int32
       size_t i = 0;
       for_each_item([&](int32_t tl, int32_t) { cost[i++] = tile_cost[tl]; });
     }
-    p->n_wg = (((8 / p->waves_per_wg) * n_cu + 7) / 8) * 8;
+    const int32_t n_wg = (((8 / p->waves_per_wg) * n_cu + 7) / 8) * 8;
     const int32_t rounds = 8 / p->waves_per_wg;
     static const int32_t four[4] = {1000, 1085, 1085, 1125}, two[2] = {1000, 1150}, one[1] = {1000};
-    hand_out(cost, p->n_wg, rounds == 4 ? four : rounds == 2 ? two : one, rounds, owner, p->wg_begin);
-    p->max_slice = 0;
-    for (int32_t i = 0; i < p->n_wg; ++i) p->max_slice = std::max(p->max_slice, p->wg_begin[i + 1] - p->wg_begin[i]);
-    p->items.resize(n_items);
-    std::vector<int32_t> at(p->wg_begin.begin(), p->wg_begin.end() - 1);
-    size_t i = 0;
-    for_each_item([&](int32_t tl, int32_t hg) {
-      p->items[at[owner[i++]]++] = make_item(all_tiles[tl], hg * p->heads_per_wg, hg * p->heads_per_wg / G);
-    });
+    std::vector<int32_t> begin;
+    hand_out(cost, n_wg, rounds == 4 ? four : rounds == 2 ? two : one, rounds, owner, begin);
+    if (few_tiles) {
+      for (int32_t &c : cost) c -= 2;                     // stages of K and V
+      p->wide = wide_ends_first(p, cost, owner, n_wg, rounds);
+    }
+    if (!p->wide) {
+      p->wide_tiles.clear();
+      p->wide_items.clear();
+      p->n_tiles = static_cast<int32_t>(all_tiles.size());
+      p->n_wg = n_wg;
+      p->wg_begin.swap(begin);
+      p->max_slice = 0;
+      for (int32_t i = 0; i < p->n_wg; ++i) p->max_slice = std::max(p->max_slice, p->wg_begin[i + 1] - p->wg_begin[i]);
+      p->items.resize(n_items);
+      std::vector<int32_t> at(p->wg_begin.begin(), p->wg_begin.end() - 1);
+      size_t i = 0;
+      for_each_item([&](int32_t tl, int32_t hg) {
+        p->items[at[owner[i++]]++] = make_item(all_tiles[tl], hg * p->heads_per_wg, hg * p->heads_per_wg / G);
+      });
+    }
   }
 
   // --- decode gather tables: shared ranges per prompt, ranges per path slot

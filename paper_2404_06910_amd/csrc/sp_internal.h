@@ -115,7 +115,7 @@ struct WideTile {
   int32_t n_keys;
   int32_t anc;         // ancestor keys
   int32_t anc_end;     // several groups: `anc` rounded up to 32; one group, whose own run follows directly: 0
-  int32_t unused;
+  int32_t steps;       // stages that each block is computed on, summed up (what a tile takes, for the host)
   WideBlock block[kWideWaves];
   WideRange range[kWideRanges];
 };

@@ -43,3 +43,21 @@ def test_plans_that_stay_with_the_other_kernel():
     cached = np.ones(len(args[1]), np.uint8)
     cached[np.flatnonzero(args[2] == 24)] = 0
     assert _slots(args, T, 32, 32, cached=cached) != WIDE_SLOTS
+
+
+# Few tiles per compute unit, us with the other kernel and with the wide one
+@pytest.mark.parametrize("Hq,Hkv,prompts,chain,docs,query,wide", [
+    (32, 32, 3, 4096, [128] * 3, 24, False),                        # 152 / 217: an eighth of the units has two tiles
+    (32, 16, 7, 2241, [25] * 3, 40, False),                         # 94 / 138: three in ten, most of them half empty
+    (32, 32, 5, 8192, [40] * 6, 8, False),                          # 350 / 443: a quarter
+    (32, 32, 6, 2524, [10] * 5, 40, False),                         # 112 / 152: half, and half tiles
+    (24, 24, 7, 3329, [705], 24, False),                            # 321 / 369: a quarter has four, the others three
+    (32, 32, 1, 32768, [250] * 4, 0, True),                         # 1060 / 933: half of the units has one, the others none
+    (32, 32, 1, 16384, [250] * 8, 0, True),                         # 646 / 548: one each
+])
+def test_few_tiles_go_where_the_slowest_unit_ends_first(Hq, Hkv, prompts, chain, docs, query, wide):
+    args, T, cached = chain_table(prompts=prompts, chain=[chain], docs=docs, query=query, gap=1, cached_chain=True)
+    assert (_slots(args, T, Hq, Hkv, cached=cached) == WIDE_SLOTS) == wide
+    names = ("prompt_seg_off", "seg_tok_start", "seg_tok_len", "seg_parent", "seg_path")
+    if T < 60000 and not wide:
+        _check_work_list(dict(zip(names, args), n_tokens=T), Hq, Hkv, cached=cached)

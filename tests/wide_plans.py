@@ -52,9 +52,9 @@ CASES = {
                                  cached_chain=True)),
     "query_apart": (32, 32, dict(prompts=6, chain=[704], docs=[256, 250, 512], query=230, query_apart=True)),
     "two_heads": (12, 6, dict(prompts=10, chain=[1100, 300], docs=[220, 100, 33, 64, 150, 31, 129, 128], query=24, gap=2)),
-    "holes": (32, 32, dict(prompts=8, chain=[2000], docs=[40] * 10, query=40, hole=100, cached_chain=True)),
+    "holes": (32, 32, dict(prompts=10, chain=[1500], docs=[40] * 10, query=40, hole=100, cached_chain=True)),
     "holes_ragged": (24, 24, dict(prompts=9, chain=[1800, 700], docs=[24, 72, 40, 1, 32, 64, 100, 33, 24, 260, 72, 24], query=24,
                                   gap=1, hole=60, cached_chain=True)),
-    "holes_of_pairs": (12, 6, dict(prompts=12, chain=[3000], docs=[24, 72, 40, 8, 100, 24], query=40, hole=33, cached_chain=True)),
+    "holes_of_pairs": (12, 6, dict(prompts=10, chain=[2000], docs=[24, 72, 40, 8, 100, 24], query=40, hole=33, cached_chain=True)),
     "five_by_two": (20, 10, dict(prompts=8, chain=[1111], docs=[220, 100, 1, 70, 200, 32], query=24)),
 }
