@@ -873,9 +873,15 @@ sp_status upload_plan(sp_ctx *ctx, sp_plan *p, void *reuse_blob, size_t reuse_by
     if (end > beg) { d.tok_start = p->dec_ranges[beg].tok_start; d.len = p->dec_ranges[beg].len; }
     return d;
   };
+  // Descriptors at a fixed stride (see build_key_table) where a launch may be small enough to look at them early: it has a
+  // workgroup per prompt and KV head at least.  With prompts of very different path counts the padding is bounded: by 64 KB, or
+  // by three times what the descriptors themselves take.
   int32_t path_stride = 0;
   for (int32_t b = 0; b < B; ++b) path_stride = std::max(path_stride, p->path_off[b + 1] - p->path_off[b]);
-  if (path_stride > 64) path_stride = 0;
+  const int64_t padded = int64_t(B) * path_stride;
+  if (path_stride > 64 || int64_t(B) * p->n_kv_heads > int64_t(sp::kDecFewWgsPerCu) * ctx->n_cu ||
+      padded > std::max<int64_t>(sp::kDecPaddedDescs, int64_t(4) * p->n_slots))
+    path_stride = 0;
   std::vector<sp::RangeDesc> shared_desc(B), path_desc(path_stride ? size_t(B) * path_stride : size_t(p->n_slots));
   for (int32_t b = 0; b < B; ++b) shared_desc[b] = describe(p->shared_rng_beg[b], p->shared_rng_end[b]);
   for (int32_t b = 0; b < B; ++b)

@@ -69,8 +69,8 @@ struct KeyTable {
 
 // One thread per source follows the tables (kept -> path slot descriptor, which carries the first range), so the
 // dependent loads of all sources run side by side; a prefix over the sources puts the ranges in order.
-// Where no prompt has more than 64 paths, the descriptors of a prompt's paths lie at a fixed place (path_stride) and the
-// first wave reads all of them while `kept` is on its way, and picks from its lanes: one memory latency less for every
+// Where no prompt has more than 64 paths, the descriptors of a prompt's paths lie at a fixed place (path_stride; upload_plan
+// says where not) and the first wave reads all of them while `kept` is on its way, and picks from its lanes: one memory latency less for every
 // launch, and no barrier between the two halves, which one wave does (four tokens of six prompts of 32/8 heads 47.0 -> 45.1 us,
 // a request with five tokens of one prompt of 32 heads 89.1 -> 86.2).  With more than four workgroups to a compute unit the
 // others' streams hide the latency, and the reads of paths that are not kept cost 0.2 % (64 prompts, 32 heads: 91.1 / 91.4).
@@ -752,7 +752,7 @@ static hipError_t launch_decode_t(const sp_plan *plan, DecodeDev &d, const Decod
   }
   d.chunks_together = ny > 1 && base % 8 == 0 && base / 8 <= 65535;
   const unsigned n_z = unsigned(d.n_pieces / d.pieces_per_wg);
-  d.few_wgs = int64_t(base) * ny * n_z <= int64_t(4) * plan->ctx->n_cu;
+  d.few_wgs = int64_t(base) * ny * n_z <= int64_t(kDecFewWgsPerCu) * plan->ctx->n_cu;
   const dim3 grid = d.chunks_together ? dim3(8u * unsigned(ny), n_z, unsigned(base) / 8) : dim3(unsigned(base), n_z, unsigned(ny));
   const dim3 block(kDecThreads);
   auto launch_as = [&](auto heads, auto bias, auto stream) {

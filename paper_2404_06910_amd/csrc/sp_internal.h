@@ -45,6 +45,10 @@ constexpr int kDecPartCounters = 1024;
 // Regions that a plan has from the start (or as many as the plan destroyed last had in use, up to kDecPlanRegions), and the
 // most that a plan may come to have.
 constexpr int kDecFirstRegions = 4, kDecPlanRegions = 32, kDecMaxRegions = 256;
+// A decode launch is small with up to this many workgroups per compute unit (build_key_table); what the descriptors of paths at
+// a fixed stride may take in any case.
+constexpr int kDecFewWgsPerCu = 4;
+constexpr int64_t kDecPaddedDescs = 4096;
 constexpr size_t kDecChunkBytes = size_t(16) << 20;
 struct DecodeRegion {
   void *part;
@@ -139,7 +143,7 @@ struct PlanDev {
   // ranges when there is only one (the usual case), without a further dependent read
   const RangeDesc *shared_desc;  // [n_prompts] the shared segments of each prompt
   const RangeDesc *path_desc;    // each path slot: [n_prompts][path_stride], or [n_slots] where path_stride is 0
-  int32_t path_stride;           // most paths of any prompt (up to 64, else 0)
+  int32_t path_stride;           // most paths of any prompt, or 0 (more than 64, or too much padding, or no small launch)
   const KeyRange *dec_ranges;
   int32_t n_items;
   int32_t n_wg;

@@ -47,3 +47,39 @@ def test_kept_tables(dtype, Hq, Hkv, counts, k):
         check_attn(o[b].float().cpu().numpy(), ref, dtype, "prompt %d" % b)
     plan.close()
     ctx.close()
+
+
+def test_prompts_of_very_different_path_counts():
+    """One prompt of 64 paths among many of one: the tables do not take a place for 64 paths of every prompt, and the look-up
+    without such places finds the same keys (300 prompts: a launch that is small enough for the other one)."""
+    n, d = 300, 64
+    counts = [1] * n
+    counts[7] = 64
+    rng = np.random.default_rng(5)
+    st = sp_synth.forkjoin_segtable(5, [[int(x) for x in rng.integers(1, 5, c)] for c in counts], 2)
+    f = lambda *s: sp_synth.round_to_dtype(rng.standard_normal(s, dtype=np.float32), "f32")
+    K, V, Kr, Vr = f(st.n_tokens, 2, d), f(st.n_tokens, 2, d), f(n, 1, 2, d), f(n, 1, 2, d)
+    q, kn, vn = f(n, 2, d), f(n, 2, d), f(n, 2, d)
+    kept = np.stack([[0, 1, -1] if c == 1 else [63, 5, 0] for c in counts]).astype(np.int32)   # path 1 only where there is one
+    ctx = B.Context(0)
+    plan = make_plan(ctx, st, 2, 2, d, "f32")
+    o = torch.zeros((n, 2, d), device="cuda")
+    ctx.sp_pruned_decode(plan, dev(kept), 3, dev(K), dev(V), dev(Kr), dev(Vr), 1, dev(q), dev(kn), dev(vn), o, 0.125)
+    torch.cuda.synchronize()
+    for b in (0, 6, 7, 8, n - 1):
+        mine = [int(x) for x in kept[b] if 0 <= x < counts[b]]
+        at = orc.joined_cache_index(st.prompt_seg_off, st.seg_tok_start, st.seg_tok_len, st.seg_path, b, mine)
+        check_attn(o[b].cpu().numpy(), orc.pruned_decode_step(q[b], kn[b], vn[b], K, V, at, Kr[b, :0], Vr[b, :0], 0.125), "f32")
+    plan.close()
+    n = 40000
+    seg = lambda first, second: np.concatenate([np.stack([np.full(n, first), np.full(n, second)], 1).ravel(), np.full(63, second)])
+    off = np.append(np.arange(0, 2 * n, 2), 2 * n + 63).astype(np.int32)      # the last prompt has 64 paths
+    parent = np.stack([np.full(n, -1), np.arange(n) * 2], 1).ravel()
+    parent, path = np.concatenate([parent, np.full(63, 2 * n - 2)]), seg(-1, 0)
+    path[2 * n:] = np.arange(1, 64)
+    free = torch.cuda.mem_get_info()[0]
+    plan = B.Plan(ctx, off, np.arange(2 * n + 63), np.ones(2 * n + 63), parent, path, 2 * n + 63, 1, 1, 64, B.SP_F32)
+    took = free - torch.cuda.mem_get_info()[0]
+    assert took < 16 << 20, took              # 32-byte items, 16-byte descriptors and a few numbers per prompt; 49 MB with places
+    plan.close()
+    ctx.close()
