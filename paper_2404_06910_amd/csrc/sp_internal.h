@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include <string>
@@ -101,21 +102,21 @@ struct WorkItem {
 // Work of the wide prefill kernel: tiles of kWideWaves blocks of up to 32 rows (over the query heads of a workgroup), and items
 // that name a tile and its heads.  The rows of a tile may belong to several row groups when these have the same ancestors; its
 // keys are one virtual sequence [ancestors ; own run of each group], cut into ranges.  With several groups every own run
-// begins at a multiple of 32 keys (a block of 32 never holds keys of two of them).
+// begins at a multiple of 32 keys (a block of 32 never holds keys of two of them).  The kernel moves them in pieces of 16 bytes.
 constexpr int kWideWaves = 8, kWideStageKeys = 64, kWideRanges = 16;
-struct WideRange {
+struct alignas(16) WideRange {
   int32_t delta;       // virtual keys from the end of the range before up to `end` are the tokens min(delta + key, last)
   int32_t end;         // the last range's has no end
   int32_t last;
   int32_t unused;
 };
-struct WideBlock {
+struct alignas(16) WideBlock {
   int32_t tok;         // first row's token
   int32_t n_rows;      // 0: none
   int32_t first;       // first row's virtual key
   int32_t base;        // first virtual key of its own run
 };
-struct WideTile {
+struct alignas(16) WideTile {
   int32_t n_keys;
   int32_t anc;         // ancestor keys
   int32_t anc_end;     // several groups: `anc` rounded up to 32; one group, whose own run follows directly: 0
@@ -123,6 +124,8 @@ struct WideTile {
   WideBlock block[kWideWaves];
   WideRange range[kWideRanges];
 };
+static_assert(sizeof(WideRange) == 16 && sizeof(WideBlock) == 16 && offsetof(WideTile, block) == 16 &&
+              offsetof(WideTile, range) == 16 + 16 * kWideWaves && sizeof(WideTile) == 16 * (1 + kWideWaves + kWideRanges));
 struct WideItem {
   int32_t tile;
   int32_t heads;       // pack_heads(first query head, its KV head)

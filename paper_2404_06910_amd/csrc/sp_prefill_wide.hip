@@ -43,6 +43,7 @@ constexpr int LROWS = 2 * BK / NP, NDMA = LROWS / 4;   // rows of a stage that a
 constexpr int NQ = NW / NP;                         // stages of Q rows
 constexpr int kBatch = 24;                         // items staged in LDS at a time
 constexpr int kTileVec = sizeof(WideTile) / 16;
+static_assert(sizeof(WideTile) % 16 == 0 && alignof(WideTile) == 16, "tiles are moved in pieces of 16 bytes");
 static_assert(NDMA == 8, "the waits count eight DMA instructions per stage");
 
 }  // namespace
