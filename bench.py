@@ -85,6 +85,16 @@ def _stored_traffic(key):
     return v
 
 
+def _prefill_kernel(plan, n_cu):
+    """The kernel that a bf16 plan's prefill takes: the wide one's work list has a slot per compute unit (rounded up to 8),
+    the other's two or four."""
+    return "prefill_wide_kernel" if len(plan.work_items()[1]) - 1 == (n_cu + 7) // 8 * 8 else "prefill_bf16_kernel"
+
+
+def _n_cu(torch):
+    return torch.cuda.get_device_properties(torch.cuda.current_device()).multi_processor_count
+
+
 def _prefill_roofline(ms, flops, bytes_, traffic_key):
     """Both roofs of one prefill launch: HBM (the binding one at these shapes) and bf16 MFMA, plus the
     fraction of min(MFMA peak, intensity x HBM peak)."""
@@ -297,6 +307,7 @@ def main():
     dec_bytes = sum(decode_step_bytes(wl.n_prompts * (kept_keys + s + 1), wl.n_kv_heads, wl.head_dim, 2) for s in range(S))
     dec_gbs = dec_bytes / (mean[3] * 1e-3) / 1e9
 
+    prefill_kernel = _prefill_kernel(plans[0], _n_cu(torch))
     out = {
         "metric": "forkjoin_prefill_tflops", "value": round(tflops, 2), "unit": "TFLOP/s", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(wall / args.steps * 1e3, 4),
@@ -309,14 +320,14 @@ def main():
         "plan_create_ms": _plan_create_ms(ctx, B, wl, st),
         # dominant kernel: prefill.  Its arithmetic intensity at this shape (flops/compulsory bytes) is
         # below the machine balance, so HBM is the binding roof; the MFMA view is given next to it.
-        "roofline": {"kernel": "prefill_bf16_kernel", "bound": "hbm", "achieved": round(pbytes / t_pre / 1e9, 1),
+        "roofline": {"kernel": prefill_kernel, "bound": "hbm", "achieved": round(pbytes / t_pre / 1e9, 1),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(pbytes / t_pre / 1e9 / HBM_PEAK_GBS, 4),
-                     "traffic": _stored_traffic("prefill_bf16_kernel:" + wl.name),
+                     "traffic": _stored_traffic(prefill_kernel + ":" + wl.name),
                      "traffic_source": "stored: profiles/traffic.json (rocprofv3 --pmc runs, not counted in this run)",
                      "algorithmic_bytes": pbytes, "algorithmic_flops": flops,
                      "intensity_flop_per_byte": round(flops / pbytes, 1), "avg_launch_ms": round(mean[0], 4),
                      "median_launch_ms": round(med[0], 4), "min_launch_ms": round(mn[0], 4)},
-        "roofline_mfma": {"kernel": "prefill_bf16_kernel", "bound": "mfma", "achieved": round(tflops, 2),
+        "roofline_mfma": {"kernel": prefill_kernel, "bound": "mfma", "achieved": round(tflops, 2),
                           "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                           "frac": round(tflops / MFMA_BF16_PEAK_TFLOPS, 4),
                           "hbm_ceiling_frac": round(flops / pbytes * HBM_PEAK_GBS * 1e9 / 1e12 / MFMA_BF16_PEAK_TFLOPS, 4)},
@@ -419,8 +430,9 @@ def _bench_workload_leg(ctx, torch, B, name, bias, saliency=True, n_warm=N_WARM,
     t = _time_launches(torch, lambda i: ctx.sp_forkjoin_prefill(plans[i % 2], *sets[i % 2], scale), n_warm, n_trials)
     flops = float(np.mean([prefill_flops(p.visible_pairs(), wl.n_q_heads, wl.head_dim) for p in plans]))
     by = float(np.mean([prefill_bytes(s[0].shape[0], wl.n_q_heads, wl.n_kv_heads, wl.head_dim, 2) for s in sets]))
-    out = {"prefill": dict(t, kernel="prefill_bf16_kernel", bound="hbm",
-                           **_prefill_roofline(t["median_ms"], flops, by, "prefill_bf16_kernel:" + name + ("+bias" if bias else ""))),
+    kernel = _prefill_kernel(plans[0], _n_cu(torch))
+    out = {"prefill": dict(t, kernel=kernel, bound="hbm",
+                           **_prefill_roofline(t["median_ms"], flops, by, kernel + ":" + name + ("+bias" if bias else ""))),
            "tokens": int(sets[0][0].shape[0]), "n_prompts": wl.n_prompts,
            "plan_create_ms": _plan_create_ms(ctx, B, wl, sts[1], tok_pos=pos, alibi_slopes=slopes)}   # pos belongs to sts[1]
     del sets, plans
@@ -480,10 +492,11 @@ def _bench_online_prefill(ctx, torch, B, wl, sets, scale, n_warm=N_WARM, n_trial
     qob = q_rows * 2 * wl.n_q_heads * wl.head_dim * 2
     flops = prefill_flops(plans[0].visible_pairs(), wl.n_q_heads, wl.head_dim)
     gbs = (kvb + qob) / (ms * 1e-3) / 1e9
-    return dict(tm, kernel="prefill_bf16_kernel", rows="query copies only", bound="hbm", achieved=round(gbs, 1),
+    kernel = _prefill_kernel(plans[0], _n_cu(torch))
+    return dict(tm, kernel=kernel, rows="query copies only", bound="hbm", achieved=round(gbs, 1),
                 peak=HBM_PEAK_GBS, unit="GB/s", frac=round(gbs / HBM_PEAK_GBS, 4), algorithmic_bytes=kvb + qob,
                 algorithmic_flops=flops, tflops=round(flops / (ms * 1e-3) / 1e12, 2),
-                traffic=_stored_traffic("prefill_bf16_kernel:" + wl.name + ":online_cached"),
+                traffic=_stored_traffic(kernel + ":" + wl.name + ":online_cached"),
                 traffic_source="stored: profiles/traffic.json",
                 plan_create_ms=_plan_create_ms(ctx, B, wl, t, seg_cached=cacheds[0]))
 
@@ -539,6 +552,7 @@ def _bench_iterative_round(ctx, torch, B, wl, sets, scale, chain=(3, 7, 11, 15),
     tm = _time_launches(torch, launch, n_warm, n_trials)
     ms = tm["median_ms"]
     flops = prefill_flops(plans[0].visible_pairs(), wl.n_q_heads, wl.head_dim)
+    kernel = _prefill_kernel(plans[0], _n_cu(torch))
     # per-round cost of the new table: the plan object is rebuilt in place (sp_plan_update)
     ts = []
     off, start, length, parent, path, cached, n_tok = tabs[0]
@@ -552,11 +566,11 @@ def _bench_iterative_round(ctx, torch, B, wl, sets, scale, chain=(3, 7, 11, 15),
     off, start, length, parent, path, cached, n_tok = tabs[0]
     rows = int(sum(int(l) for l, c in zip(length, cached) if not c))
     by = n_tok * kv_bytes_per_token(wl.n_kv_heads, wl.head_dim, 2) + rows * 2 * wl.n_q_heads * wl.head_dim * 2
-    return dict(tm, kernel="prefill_wide_kernel", rows="documents not yet kept and their query copies",
+    return dict(tm, kernel=kernel, rows="documents not yet kept and their query copies",
                 chain_documents=len(chain), algorithmic_flops=flops, tflops=round(flops / (ms * 1e-3) / 1e12, 2),
                 algorithmic_bytes=by, hbm_frac=round(by / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                 mfma_frac=round(flops / (ms * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS, 4),
-                traffic=_stored_traffic("prefill_wide_kernel:" + wl.name + ":iterative_round"),
+                traffic=_stored_traffic(kernel + ":" + wl.name + ":iterative_round"),
                 traffic_source="stored: profiles/traffic.json",
                 plan_update_ms=round(float(np.median(ts[2:])) * 1e3, 3))
 

@@ -2,6 +2,7 @@
 import numpy as np
 import pytest
 
+import bench
 import sp_synth
 from paper_2404_06910_amd import binding as B
 
@@ -61,3 +62,12 @@ def test_few_tiles_go_where_the_slowest_unit_ends_first(Hq, Hkv, prompts, chain,
     names = ("prompt_seg_off", "seg_tok_start", "seg_tok_len", "seg_parent", "seg_path")
     if T < 60000 and not wide:
         _check_work_list(dict(zip(names, args), n_tokens=T), Hq, Hkv, cached=cached)
+
+
+def test_the_benchmark_names_the_kernel_that_the_plan_takes():
+    for prompts, name in ((8, "prefill_wide_kernel"), (1, "prefill_bf16_kernel")):
+        args, T, _ = chain_table(prompts=prompts, chain=[600], docs=[128] * 12, query=24)
+        for heads in ((32, 32), (32, 8)):                           # grouped heads: two slots per compute unit
+            p = B.Plan(None, *args, T, *heads, 128, B.SP_BF16)
+            assert bench._prefill_kernel(p, 256) == (name if heads == (32, 32) else "prefill_bf16_kernel")
+            p.close()
