@@ -360,7 +360,7 @@ void hand_out(const std::vector<int32_t> &cost, int32_t n_slots, const int32_t *
 // The fit holds for tiles whose waves compute on most stages (three quarters and more in those plans).  A tile of eight short
 // query copies behind their own cached documents streams eight documents for all and computes on a sixth: 24 rows behind 64 +
 // 128 keys 104 us with the other kernel and 108 here, behind 64 + 64 to 220 110 and 118, behind 300 + 128 (a third) 129 and 128.
-// So at least half of the stages have to be computed on.
+// So at least half of the stages have to be computed on, on average over a tile's waves.
 //
 // These are means over the compute units.  With few tiles to a unit the slowest unit decides, see wide_ends_first.
 void wide_tiles(sp_plan *p, const std::vector<std::vector<std::pair<int32_t, int32_t>>> &live_rows,
