@@ -363,7 +363,7 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_bf16_kernel(PlanDev pd, co
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             const int rows_here = min(32, cur.n_rows - r0);
-            __bf16 *ob = O + ((uint64_t)(uint32_t)(cur.tok_start + cur.row0 + r0) * q_ts + (uint32_t)head * q_hs);
+            __bf16 *ob = O + ((uint64_t)(uint32_t)(cur.tok_start + cur.row0 + r0) * q_ts + (uint64_t)(uint32_t)head * q_hs);
 #pragma unroll
             for (int i = 0; i < 32 * CPR / 64; ++i) {
               const int id = lane + 64 * i, row = id / CPR, ch = id % CPR;

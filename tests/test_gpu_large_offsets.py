@@ -65,3 +65,29 @@ def test_prompts_behind_the_4GB_mark():
     mx, mean = attn_tol("bf16")
     assert err.max() <= mx and err.mean() <= mean
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 64)])
+def test_heads_further_apart_than_32_bits(dtype, d):
+    """Head and token strides of 2^25 elements and a little more: heads from 128 on lie behind element 2^32 of Q and O."""
+    print("case:", dtype, d, flush=True)
+    H, hs, ts = 140, 1 << 25, (1 << 25) + 128
+    st = sp_synth.forkjoin_segtable(3, [[4, 2]], 1)
+    T = st.n_tokens
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    Qc, K, V = (torch.randn((T, H, d), generator=g, device="cuda", dtype=dt) for _ in range(3))
+    far = lambda: torch.as_strided(torch.empty((T - 1) * ts + (H - 1) * hs + d, device="cuda", dtype=dt), (T, H, d), (ts, hs, 1))
+    Q, O, Oc = far(), far(), torch.zeros_like(Qc)
+    Q.copy_(Qc)
+    O.zero_()
+    ctx = B.Context(0)
+    plan = B.Plan(ctx, st.prompt_seg_off, st.seg_tok_start, st.seg_tok_len, st.seg_parent, st.seg_path, T, H, H, d,
+                  B.SP_BF16 if dtype == "bf16" else B.SP_F32)
+    ctx.sp_forkjoin_prefill(plan, Q, K, V, O, 0.1)
+    ctx.sp_forkjoin_prefill(plan, Qc, K, V, Oc, 0.1)
+    torch.cuda.synchronize()
+    assert torch.equal(O, Oc)
+    plan.close()
+    ctx.close()
